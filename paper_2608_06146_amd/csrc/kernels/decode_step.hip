@@ -64,6 +64,8 @@ template <int D>
 __device__ __forceinline__ void private_item(const TileParams& p, int item, int lane) {
   constexpr int NDS = D / 32;  // K-slices (32 d each) of the score product
   constexpr int NDM = D / 16;  // 16-row blocks of O^T
+  // furthest element of a Q row that a load past the last step reads (load_v)
+  static_assert((NDS - 1) * 32 + 8 * 3 + 8 <= D, "loads past the last step stay in the Q row");
   const WorkRec w = load_scalar(p.work + item);
   // A one-range, one-token item without limits carries its range and its Q
   // row in the work record: its first loads wait for one record, not three.
@@ -135,7 +137,8 @@ __device__ __forceinline__ void private_item(const TileParams& p, int item, int 
   };
   // Loads of set X for the load cursor's step.  Past the item's last step
   // (real = false) the same loads read this lane's Q row instead (cached,
-  // in bounds, never used): every step issues the same loads, so the
+  // in bounds -- qp already holds 8g, so its 32-dim slices are the furthest
+  // a load may go -- and never used): every step issues the same loads, so the
   // compiler's waits for a set stay exact (a load under a branch would make
   // it wait for every load in flight).
   auto load_k = [&](int X, bool real) __attribute__((always_inline)) {
@@ -157,7 +160,7 @@ __device__ __forceinline__ void private_item(const TileParams& p, int item, int 
     const uint16_t* vp = Vc + ((blk[X][g >> 1] * Hkv + kvh) * D + n) * kBlock + 8 * (g & 1);
 #pragma unroll
     for (int dm = 0; dm < NDM; ++dm)
-      vf[X][dm] = load_stream16(real ? vp + dm * 16 * kBlock : qp + dm * 16);
+      vf[X][dm] = load_stream16(real ? vp + dm * 16 * kBlock : qp + (dm % NDS) * 32);
     vkeep[X] = keep;
   };
 
