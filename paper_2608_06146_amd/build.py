@@ -28,7 +28,7 @@ SOURCES = [
     "csrc/abi.hip",
     "csrc/kernels/tile_mfma_bf16.hip",
     "csrc/kernels/decode_step.hip",
-    "csrc/kernels/tile_valu_f32.hip",
+    "csrc/kernels/tile_f32.hip",
     "csrc/kernels/lse_combine.hip",
     "csrc/kernels/bwd.hip",
     "csrc/kernels/append.hip",
