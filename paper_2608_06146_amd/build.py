@@ -33,6 +33,7 @@ SOURCES = [
     "csrc/kernels/bwd.hip",
     "csrc/kernels/append.hip",
     "csrc/kernels/relayout.hip",
+    "csrc/kernels/upload.hip",
 ]
 # Every header under csrc/ (and the public header) enters each object's
 # digest, so an edit to any of them rebuilds every object.

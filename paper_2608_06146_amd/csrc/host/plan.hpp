@@ -59,9 +59,9 @@ struct padoc_plan {
   // Incremented by every build of the plan (plans rebuilt in place).
   uint64_t build_id = 0;
 
-  // Pinned host copy of `blob` (made on the first launch after a build, so
-  // the schedule upload is a true asynchronous DMA; freed by
-  // padoc_plan_destroy), the build it holds, and for rebuilt plans an event
+  // Pinned host copy of `blob` (made on the first launch after a build, read
+  // over the bus by the upload kernel; freed by padoc_plan_destroy), the build
+  // it holds, and for rebuilt plans an event
   // (hipEvent_t) after the last upload that read it.
   mutable std::mutex pin_mu;
   mutable void* pinned = nullptr;
