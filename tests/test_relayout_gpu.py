@@ -86,3 +86,28 @@ def test_cache_from_rows_errors():
     assert lib.padoc_cache_from_rows(p, p, p, p, 2, 1, 64, _lib.BF16, None) == _lib.ERR_ARG     # in place
     assert lib.padoc_cache_from_rows(p, p, None, None, 2, 1, 96, _lib.BF16, None) == _lib.ERR_SHAPE
     assert lib.padoc_cache_from_rows(None, None, None, None, 0, 1, 64, _lib.BF16, None) == _lib.OK  # nothing to do
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 64), ("f32", 128)])
+@pytest.mark.parametrize("nb,hkv,shift", [(1, 1, 0), (3, 1, 1), (5, 3, 1), (129, 2, 3)])
+def test_cache_from_rows_counts_and_alignment(dtype, d, nb, hkv, shift):
+    """Block counts around the (block, head) pairs a workgroup takes at once,
+    in buffers that start `shift` elements past an aligned address; nothing
+    outside the destinations is written."""
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    n = nb * hkv * 16 * d
+    kr, vr = _rows(nb, hkv, d, dtype, 3), _rows(nb, hkv, d, dtype, 4)
+    bufs = [torch.full((n + 16,), 7.0, dtype=t, device="cuda") for _ in range(4)]
+    bufs[0][shift:shift + n] = kr.reshape(-1)
+    bufs[1][shift:shift + n] = vr.reshape(-1)
+    view = [b[shift:shift + n] for b in bufs]
+    print(f"[case] relayout {dtype} d={d} Hkv={hkv} blocks={nb} shift={shift}", flush=True)
+    pa.cache_from_rows(view[0].view(nb, hkv, 16, d), view[1].view(nb, hkv, 16, d), view[2].view(nb, hkv, d // 8, 16, 8),
+                       view[3].view(nb, hkv, d, 16))
+    torch.cuda.synchronize()
+    slot = [int(od.chunk_slot(np.array([i]))[0]) for i in range(16)]  # its own inverse
+    k = kr.view(nb, hkv, 16, d // 8, 8).permute(0, 1, 3, 2, 4)[:, :, :, slot]
+    assert torch.equal(view[2].view(nb, hkv, d // 8, 16, 8), k)
+    assert torch.equal(view[3].view(nb, hkv, d, 16), vr.transpose(2, 3))
+    for b in bufs[2:]:
+        assert bool((b[:shift] == 7).all()) and bool((b[shift + n:] == 7).all())
