@@ -61,8 +61,8 @@ SQ_PASSES = {
     "sqC": "SQ_INSTS_MFMA SQ_INSTS_VALU SQ_INSTS_SALU SQ_INSTS_VMEM_RD SQ_INSTS_SMEM SQ_ACTIVE_INST_VMEM "
            "SQ_ACTIVE_INST_SCA SQ_INSTS_BRANCH GRBM_GUI_ACTIVE",
 }
-SQ_KERNELS = (FORWARD_KERNEL, DECODE_KERNELS[0], "bwd_dkdv_kernel<128>", "bwd_dq_kernel<128>")
-BACKWARD_KERNELS = ("bwd_prep_kernel<128>", "bwd_dq_kernel<128>", "bwd_dkdv_kernel<128>", "bwd_finalize_kernel")
+SQ_KERNELS = (FORWARD_KERNEL, DECODE_KERNELS[0], "bwd_dkdv_kernel<128, false>", "bwd_dq_kernel<128>")
+BACKWARD_KERNELS = ("bwd_tokens_kernel", "bwd_dq_kernel<128>", "bwd_dkdv_kernel<128, false>", "bwd_reduce_kernel<128>")
 COPY_KERNEL = "__amd_rocclr_copyBuffer"
 COPY_BYTES = 1 << 30
 

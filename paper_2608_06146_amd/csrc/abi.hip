@@ -388,18 +388,23 @@ extern "C" padoc_status padoc_tree_attn_bwd(const padoc_plan* plan, const void* 
   bp.dq = dq;
   bp.dk = dk;
   bp.dv = dv;
-  bp.dd = reinterpret_cast<float*>(ws + plan->bws_off_dd);
-  bp.dk_acc = reinterpret_cast<float*>(ws + plan->bws_off_dk);
-  bp.dv_acc = reinterpret_cast<float*>(ws + plan->bws_off_dv);
+  bp.nl = reinterpret_cast<float*>(ws + plan->bws_off_nl);
+  bp.nd = reinterpret_cast<float*>(ws + plan->bws_off_nd);
+  bp.part = reinterpret_cast<float*>(ws + plan->bws_off_part);
   bp.work = at<WorkRec>(ws, plan->off_work);
   bp.ranges = at<RangeRec>(ws, plan->off_ranges);
   bp.lims = at<int32_t>(ws, plan->off_lims);
   bp.toks = at<int32_t>(ws, plan->off_toks);
   bp.bwd = at<BwdRec>(ws, plan->bws_off_blob + plan->boff_bwd);
-  bp.btoks = at<int32_t>(ws, plan->bws_off_blob + plan->boff_btoks);
-  bp.blims = at<int32_t>(ws, plan->bws_off_blob + plan->boff_blims);
+  bp.btokens = at<BwdTokens>(ws, plan->bws_off_blob + plan->boff_btokens);
+  bp.breduce = at<BwdReduce>(ws, plan->bws_off_blob + plan->boff_breduce);
+  bp.btoks = reinterpret_cast<int32_t*>(ws + plan->bws_off_btoks);
+  bp.blims = reinterpret_cast<int32_t*>(ws + plan->bws_off_blims);
+  bp.n_btokens = (int32_t)plan->btokens.size();
+  bp.n_breduce = (int32_t)plan->breduce.size();
   bp.n_q = plan->num_q_rows;
   bp.T = plan->num_kv_rows;
+  bp.n_btok = plan->n_btok;
   bp.Hq = plan->Hq;
   bp.Hkv = plan->Hkv;
   bp.G = plan->G;

@@ -18,6 +18,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <limits>
 #include <map>
 #include <memory>
@@ -440,79 +441,145 @@ void build_forward(padoc_plan& P, Builder& B) {
   }
 }
 
+// A run of up to kBwdKeys keys of one segment and the columns that see it.
+struct BwdRun {
+  int64_t key_row0;
+  int32_t nk, tok_begin, ntok;
+};
+
+// 32-column blocks of the longest piece a key run is cut into.  Items run one
+// per compute unit, longest first; a piece beyond the first costs its start
+// and end, about four 64-column steps, and its sums go through memory.  Few
+// candidates between a sixth of a unit's share of all blocks and no cut are
+// tried on the greedy assignment the dispatch makes of them, and the one with
+// the earliest end is taken (the longest on a tie); never under 64 blocks.
+int64_t bwd_piece_blocks(const std::vector<BwdRun>& runs, int64_t G, int64_t Hkv, int64_t units) {
+  int64_t total = 0, longest = 0;
+  for (const BwdRun& r : runs) {
+    const int64_t blocks = ceil_div((int64_t)r.ntok * G, 32);
+    total += blocks * Hkv;
+    longest = std::max(longest, blocks);
+  }
+  const int64_t share = ceil_div(total, units);
+  if (runs.size() > 20000) return std::max<int64_t>(64, share);  // many more runs than units: already even
+  int64_t best = 0, best_end = std::numeric_limits<int64_t>::max();
+  std::vector<int64_t> cost, load;
+  for (const double f : {1e9, 2.0, 1.5, 1.2, 1.0, 0.85, 0.7, 0.6, 0.5, 0.42, 0.35, 0.3, 0.25, 0.2, 0.167}) {
+    const int64_t cap = std::max<int64_t>(64, f > 1e6 ? longest : (int64_t)(f * (double)share));
+    cost.clear();
+    int64_t split = 0;
+    for (const BwdRun& r : runs) {
+      const int64_t blocks = ceil_div((int64_t)r.ntok * G, 32), pieces = ceil_div(blocks, cap);
+      const int64_t step = ceil_div(blocks, pieces);
+      if (pieces > 1) split += pieces * Hkv;
+      for (int64_t b = 0; b < blocks; b += step) cost.push_back(ceil_div(std::min(step, blocks - b), 2) + 4);
+    }
+    std::sort(cost.begin(), cost.end(), std::greater<int64_t>());
+    load.assign((size_t)units, 0);  // min-heap of the units' ends
+    for (const int64_t c : cost)
+      for (int64_t g = 0; g < Hkv; ++g) {
+        std::pop_heap(load.begin(), load.end(), std::greater<int64_t>());
+        load.back() += c;
+        std::push_heap(load.begin(), load.end(), std::greater<int64_t>());
+      }
+    const int64_t end = *std::max_element(load.begin(), load.end()) + split / 32;
+    if (end < best_end) {
+      best_end = end;
+      best = cap;
+    }
+  }
+  return best;
+}
+
 // Backward (packed bf16): key-major items.  For each segment t and each run of
 // up to kBwdKeys of its keys [kb, kb+nk), the query tokens that see any of
 // them: t's own queries at positions p >= kb (they see keys <= p), and every
 // query of every descendant s whose fork offset into t, F(s, t), exceeds kb
 // (they see keys < F).  Each token's limit is stored relative to kb and
 // clipped to nk.  A run's columns (token x head) form one item per KV head,
-// except that runs longer than about one compute unit's share of all the
-// 32-column blocks (total / (target_workgroups / 4), at least 64 blocks) are
-// cut into equal block-aligned pieces, whose items add into the same dK/dV
-// rows; whole runs store their rows.
-void build_backward(padoc_plan& P, const AncList& anc, int32_t target_workgroups) {
+// or, in longer runs (bwd_piece_blocks), equal block-aligned pieces, each with
+// a slot for its sums, which are added up afterwards; whole runs write their
+// rows.  K/V rows that no run covers get zero.
+bool build_backward(padoc_plan& P, const AncList& anc, int32_t target_workgroups) {
   const int32_t n = (int32_t)P.seg.size();
   std::vector<std::vector<std::pair<int32_t, int32_t>>> desc(n);  // (s, F(s, t)) per t
   for (int32_t s = 0; s < n; ++s)
-    for (const auto& a : anc[s]) desc[a.first].push_back({s, a.second});
-  auto qrow = [&](int32_t s, int32_t p) {
-    const padoc_segment& sg = P.seg[s];
-    return (int32_t)(sg.q_off + (p - (sg.len - sg.q_len)));
-  };
-  struct Run {
-    int64_t key_row0;
-    int32_t nk, tok_begin, ntok, lim_begin;
-  };
-  std::vector<Run> runs;
-  int64_t total_blocks = 0;
+    if (P.seg[s].q_len > 0)
+      for (const auto& a : anc[s]) desc[a.first].push_back({s, a.second});
+  std::vector<BwdRun> runs;
+  int64_t n_btok = 0;
   for (int32_t t = 0; t < n; ++t) {
     const padoc_segment& tg = P.seg[t];
     for (int32_t kb = 0; kb < tg.len; kb += kBwdKeys) {
       const int32_t nk = std::min(kBwdKeys, tg.len - kb);
-      const int32_t tok_begin = (int32_t)P.btoks.size(), lim_begin = (int32_t)P.blims.size();
-      for (int32_t p = std::max(kb, tg.len - tg.q_len); p < tg.len; ++p) {
-        P.btoks.push_back(qrow(t, p));
-        P.blims.push_back(std::min(p + 1 - kb, nk));
+      const int64_t begin = n_btok;
+      const int32_t p0 = std::max(kb, tg.len - tg.q_len);
+      if (p0 < tg.len) {
+        P.btokens.push_back({(int32_t)n_btok, (int32_t)(tg.q_off + (p0 - (tg.len - tg.q_len))), tg.len - p0, p0 + 1 - kb, 1, nk});
+        n_btok += tg.len - p0;
       }
       for (const auto& d : desc[t]) {
+        if (d.second <= kb) continue;
         const padoc_segment& sg = P.seg[d.first];
-        if (d.second <= kb || sg.q_len == 0) continue;
-        for (int32_t p = sg.len - sg.q_len; p < sg.len; ++p) {
-          P.btoks.push_back(qrow(d.first, p));
-          P.blims.push_back(std::min(d.second - kb, nk));
-        }
+        P.btokens.push_back({(int32_t)n_btok, (int32_t)sg.q_off, sg.q_len, std::min(d.second - kb, nk), 0, nk});
+        n_btok += sg.q_len;
       }
-      const int32_t ntok = (int32_t)P.btoks.size() - tok_begin;
-      if (ntok == 0) continue;
-      runs.push_back({tg.kv_off + kb, nk, tok_begin, ntok, lim_begin});
-      total_blocks += ceil_div((int64_t)ntok * P.G, 32) * P.Hkv;
+      if (n_btok > kI32Max) return false;
+      if (n_btok > begin) runs.push_back({tg.kv_off + kb, nk, (int32_t)begin, (int32_t)(n_btok - begin)});
     }
   }
+  P.n_btok = n_btok;
   const int64_t tw = target_workgroups > 0 ? target_workgroups : 1024;
-  const int64_t cap = std::max<int64_t>(64, ceil_div(total_blocks * 4, tw));
-  for (const Run& r : runs) {
+  const int64_t cap = bwd_piece_blocks(runs, P.G, P.Hkv, std::max<int64_t>(1, std::min<int64_t>(tw / 4, 1 << 16)));
+  std::vector<std::pair<padoc::BwdRec, int32_t>> items;  // with their slots
+  for (const BwdRun& r : runs) {
     const int64_t cols = (int64_t)r.ntok * P.G;
     const int64_t blocks = ceil_div(cols, 32);
     const int64_t pieces = ceil_div(blocks, cap);
     const int64_t step = ceil_div(blocks, pieces) * 32;
-    for (int64_t c0 = 0; c0 < cols; c0 += step) {
-      for (int32_t g = 0; g < P.Hkv; ++g) {
+    const int32_t n_slots = step < cols ? (int32_t)ceil_div(cols, step) : 0;
+    for (int32_t g = 0; g < P.Hkv; ++g) {
+      if (n_slots > 0) P.breduce.push_back({r.key_row0, r.nk, g, (int32_t)(P.n_bwd_slots + (int64_t)g * n_slots), n_slots});
+      for (int64_t c0 = 0; c0 < cols; c0 += step) {
         padoc::BwdRec b{};
         b.key_row0 = r.key_row0;
         b.n_keys = r.nk;
         b.tok_begin = r.tok_begin;
         b.ntok = r.ntok;
-        b.lim_begin = r.lim_begin;
+        b.lim_begin = r.tok_begin;
         b.col0 = (int32_t)c0;
         b.ncol = (int32_t)std::min<int64_t>(step, cols - c0);
         b.kvh = g;
         b.cost = (int32_t)ceil_div(b.ncol, 32);
-        P.bwd.push_back(b);
+        items.push_back({b, n_slots > 0 ? (int32_t)(P.n_bwd_slots + (int64_t)g * n_slots + c0 / step) : -1});
       }
     }
+    P.n_bwd_slots += (int64_t)n_slots * P.Hkv;
+    if (P.n_bwd_slots > kI32Max || (int64_t)items.size() > kI32Max) return false;
   }
-  std::stable_sort(P.bwd.begin(), P.bwd.end(),
-                   [](const padoc::BwdRec& a, const padoc::BwdRec& b) { return a.cost > b.cost; });
+  std::stable_sort(items.begin(), items.end(), [](const auto& a, const auto& b) { return a.first.cost > b.first.cost; });
+  P.bwd.reserve(items.size());
+  P.bwd_slot.reserve(items.size());
+  for (const auto& it : items) {
+    P.bwd.push_back(it.first);
+    P.bwd_slot.push_back(it.second);
+  }
+  // Rows outside every run, in pieces of at most kBwdKeys.
+  std::sort(runs.begin(), runs.end(), [](const BwdRun& a, const BwdRun& b) { return a.key_row0 < b.key_row0; });
+  int64_t at = 0;
+  auto zero_to = [&](int64_t end) {
+    while (at < end) {
+      const int32_t rows = (int32_t)std::min<int64_t>(kBwdKeys, end - at);
+      P.breduce.push_back({at, rows, 0, 0, 0});
+      at += rows;
+    }
+  };
+  for (const BwdRun& r : runs) {
+    zero_to(r.key_row0);
+    at = std::max(at, r.key_row0 + r.nk);
+  }
+  zero_to(P.num_kv_rows);
+  return (int64_t)P.breduce.size() <= kI32Max && (int64_t)P.btokens.size() <= kI32Max;
 }
 
 // Decode.  A segment is shared when a query token of another segment sees
@@ -826,24 +893,30 @@ void put(std::vector<unsigned char>& blob, size_t off, const std::vector<T>& v) 
   if (!v.empty()) std::memcpy(blob.data() + off, v.data(), v.size() * sizeof(T));
 }
 
-// Backward workspace: the forward schedule (dQ items), the backward
-// schedule, then sum(dO * O) per (row, head) and the fp32 dK / dV
-// accumulators.
+// Backward workspace: the forward schedule (dQ items), the backward schedule,
+// the token lists written out, two values per (query row, head), and the sums
+// of the pieces of split runs.
 void serialise_backward(padoc_plan& P) {
   P.boff_bwd = 0;
-  P.boff_btoks = align256(P.boff_bwd + P.bwd.size() * sizeof(padoc::BwdRec));
-  P.boff_blims = align256(P.boff_btoks + P.btoks.size() * 4);
-  const size_t bytes = P.boff_blims + P.blims.size() * 4;
+  P.boff_btokens = align256(P.boff_bwd + P.bwd.size() * sizeof(padoc::BwdRec));
+  P.boff_breduce = align256(P.boff_btokens + P.btokens.size() * sizeof(padoc::BwdTokens));
+  const size_t bytes = P.boff_breduce + P.breduce.size() * sizeof(padoc::BwdReduce);
   P.bwd_blob.assign(bytes, 0);
   put(P.bwd_blob, P.boff_bwd, P.bwd);
-  put(P.bwd_blob, P.boff_btoks, P.btoks);
-  put(P.bwd_blob, P.boff_blims, P.blims);
+  put(P.bwd_blob, P.boff_btokens, P.btokens);
+  put(P.bwd_blob, P.boff_breduce, P.breduce);
+  padoc::BwdRec* rec = reinterpret_cast<padoc::BwdRec*>(P.bwd_blob.data());
+  for (size_t i = 0; i < P.bwd.size(); ++i) rec[i].cost = P.bwd_slot[i];
+  const size_t rows = (size_t)P.num_q_rows * P.Hq * 4;
   P.bws_off_blob = align256(P.blob.size());
-  P.bws_off_dd = align256(P.bws_off_blob + bytes);
-  P.bws_off_dk = align256(P.bws_off_dd + (size_t)P.num_q_rows * P.Hq * 4);
-  const size_t acc = (size_t)P.num_kv_rows * P.Hkv * P.D * 4;
-  P.bws_off_dv = align256(P.bws_off_dk + acc);
-  P.bws_bytes = std::max<size_t>(256, align256(P.bws_off_dv + acc));
+  P.bws_off_btoks = align256(P.bws_off_blob + bytes);
+  P.bws_off_blims = align256(P.bws_off_btoks + (size_t)P.n_btok * 4);
+  P.bws_off_nl = align256(P.bws_off_blims + (size_t)P.n_btok * 4);
+  P.bws_off_nd = align256(P.bws_off_nl + rows);
+  P.bws_off_part = align256(P.bws_off_nd + rows);
+  const size_t part = (size_t)P.n_bwd_slots * 2 * kBwdKeys * P.D * 4;
+  const size_t floor = 2 * (size_t)P.num_kv_rows * P.Hkv * P.D * 4;  // what callers that size it themselves expect
+  P.bws_bytes = std::max<size_t>(256, align256(P.bws_off_part + std::max(part, floor)));
 }
 
 void serialise(padoc_plan& P) {
@@ -916,14 +989,18 @@ padoc_status build_plan(const padoc_tree_desc* d, padoc_plan& P) {
       P.tc_built = false;
       P.tile_class.clear();
       P.tile_class_off.clear();
+      P.btoks.clear();
+      P.blims.clear();
     }
     P.comb_ptr.clear();
     P.comb_slot.clear();
     P.comb_rows.clear();
     P.n_slots = 0;
     P.bwd.clear();
-    P.btoks.clear();
-    P.blims.clear();
+    P.bwd_slot.clear();
+    P.btokens.clear();
+    P.breduce.clear();
+    P.n_btok = P.n_bwd_slots = 0;
     P.bwd_blob.clear();
     P.blob.clear();
     Scratch& S = t_scratch;
@@ -963,9 +1040,7 @@ padoc_status build_plan(const padoc_tree_desc* d, padoc_plan& P) {
     if (P.kind == 0) sort_by_cost(P.work, S.tmp);
     serialise(P);
     if (P.kind == 0 && P.dtype == PADOC_BF16) {
-      build_backward(P, anc, d->target_workgroups);
-      if ((int64_t)P.btoks.size() > kI32Max || (int64_t)P.bwd.size() > kI32Max)
-        return set_error(PADOC_ERR_ARG, "backward schedule too large");
+      if (!build_backward(P, anc, d->target_workgroups)) return set_error(PADOC_ERR_ARG, "backward schedule too large");
       serialise_backward(P);
     }
   } catch (const std::bad_alloc&) {
@@ -1153,7 +1228,8 @@ extern "C" padoc_status padoc_plan_export(const padoc_plan* P, padoc_schedule_vi
   v->n_tok = (int32_t)P->toks.size();
   v->toks = P->toks.data();
   // Tile classes are derived from the ranges on the first export (the
-  // kernels classify tiles from n_keys and min_lim themselves).
+  // kernels classify tiles from n_keys and min_lim themselves), and the
+  // backward's token lists from their compact form (as on the device).
   {
     std::lock_guard<std::mutex> lk(P->tc_mu);
     if (!P->tc_built) {
@@ -1164,6 +1240,13 @@ extern "C" padoc_status padoc_plan_export(const padoc_plan* P, padoc_schedule_vi
         for (int32_t kt = 0; kt < nkt; ++kt)
           P->tile_class.push_back((int64_t)(kt + 1) * P->tile_keys <= r.min_lim ? 1 : 2);
       }
+      P->btoks.reserve((size_t)P->n_btok);
+      P->blims.reserve((size_t)P->n_btok);
+      for (const auto& k : P->btokens)
+        for (int32_t i = 0; i < k.count; ++i) {
+          P->btoks.push_back(k.row0 + i);
+          P->blims.push_back((int32_t)std::min<int64_t>((int64_t)k.lim0 + (int64_t)k.slope * i, k.lim_max));
+        }
       P->tc_built = true;
     }
   }

@@ -40,12 +40,21 @@ struct padoc_plan {
   std::vector<int32_t> comb_rows;  // (row*Hkv + kvh) pairs the combine kernel merges
   int64_t n_slots = 0;
 
-  // Backward (packed bf16 plans): key-major items and their token lists.
+  // Backward (packed bf16 plans): key-major items, their token lists in
+  // compact form, and what follows them (sums of split runs, rows without
+  // queries).
   std::vector<padoc::BwdRec> bwd;
-  std::vector<int32_t> btoks, blims;
-  std::vector<unsigned char> bwd_blob;  // bwd, btoks, blims (uploaded by padoc_tree_attn_bwd)
-  size_t boff_bwd = 0, boff_btoks = 0, boff_blims = 0;
-  size_t bws_off_blob = 0, bws_off_dd = 0, bws_off_dk = 0, bws_off_dv = 0, bws_bytes = 0;
+  std::vector<int32_t> bwd_slot;  // partial slot of item i, -1: none
+  std::vector<padoc::BwdTokens> btokens;
+  std::vector<padoc::BwdReduce> breduce;
+  int64_t n_btok = 0, n_bwd_slots = 0;
+  // Export only: the token lists written out, on the first padoc_plan_export
+  // after a build (under tc_mu).
+  mutable std::vector<int32_t> btoks, blims;
+  std::vector<unsigned char> bwd_blob;  // bwd, btokens, breduce (uploaded by padoc_tree_attn_bwd)
+  size_t boff_bwd = 0, boff_btokens = 0, boff_breduce = 0;
+  size_t bws_off_blob = 0, bws_off_btoks = 0, bws_off_blims = 0, bws_off_nl = 0, bws_off_nd = 0, bws_off_part = 0;
+  size_t bws_bytes = 0;
   mutable std::once_flag bpin_once;
   mutable void* bpinned = nullptr;
 

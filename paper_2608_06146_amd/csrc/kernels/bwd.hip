@@ -10,17 +10,16 @@
 //   dS_ij = P_ij (dP_ij - D_i)
 //   dQ_i  = scale sum_j dS_ij k_j,   dK_j = scale sum_i dS_ij q_i
 // Four kernels:
-//   bwd_prep   D per (row, head); zero the fp32 dK / dV accumulators
-//   bwd_dq     query-major: the forward's work items (256 columns x the
-//              item's key ranges); per 64-key tile S^T, dP^T, dS^T and
-//              dQ^T += K^T dS^T; dQ is complete per item and written directly
-//   bwd_dkdv   key-major: up to 128 keys of one segment against the query
-//              columns that see them, 32 columns per step; waves 4-7 compute
-//              S and P for 32 keys each and dK^T += Q^T dS, waves 0-3
-//              dV^T += dO^T P for the same keys with P handed over through
-//              LDS; results go to fp32 rows (stored by an item that holds the
-//              whole run, added by the pieces of a split run)
-//   bwd_finalize  fp32 accumulators -> bf16 dK, dV (round to nearest even)
+//   bwd_tokens  the key-major items' token lists, from their compact form
+//   bwd_dq      query-major: the forward's work items (256 columns x the
+//               item's key ranges); per 64-key tile S^T, dP^T, dS^T and
+//               dQ^T += K^T dS^T; dQ is complete per item and written directly.
+//               Its columns' D and LSE are kept for bwd_dkdv.
+//   bwd_dkdv    key-major: up to 128 keys of one segment against the query
+//               columns that see them, 64 columns per step; every wavefront
+//               holds dK and dV of 32 keys and takes 32 of the step's columns
+//   bwd_reduce  sums of the pieces of split key runs -> bf16 dK, dV (round to
+//               nearest even); zero rows where no query sees a key
 // All products are v_mfma_f32_32x32x16_bf16 with fp32 accumulation.  An
 // operand whose contraction index is not contiguous in memory (K^T for dQ,
 // dO^T and Q^T for dV and dK) is read from its row-major LDS block with the
@@ -28,10 +27,12 @@
 // supplies the address of 4 consecutive elements and lane 4a+b receives
 // element b of the pieces of lanes a, 4+a, 8+a and 12+a), two reads per
 // operand, in the key / column order of the probabilities' registers.
+#include <stddef.h>
+
 #include <algorithm>
 
 #include "device_common.hpp"
-#include "tile_common.hpp"
+#include "fwd_item.hpp"
 
 namespace padoc {
 
@@ -57,26 +58,19 @@ __device__ __forceinline__ int swizzled_chunk(int r, int c) {
   return c ^ sw;
 }
 
-// ------------------------------------------------------------------ prep
+// ------------------------------------------------------------------ token lists
 
-template <int D>
-__global__ __launch_bounds__(256) void bwd_prep_kernel(BwdParams p, int64_t n_rows, int64_t n_acc4) {
+// The key-major items' token lists (query row and limit per token) from their
+// compact form, one wavefront per piece: the lists of the 8-page sample are
+// 6 MB, 100 us over the bus, their pieces 0.2 MB.
+__global__ __launch_bounds__(256) void bwd_tokens_kernel(BwdParams p) {
   const int lane = threadIdx.x & 63;
-  const int64_t nwaves = (int64_t)gridDim.x * 4;
-  for (int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); r < n_rows; r += nwaves) {
-    const uint16_t* o = static_cast<const uint16_t*>(p.o) + r * D;
-    const uint16_t* g = static_cast<const uint16_t*>(p.dout) + r * D;
-    float acc = 0.f;
-#pragma unroll
-    for (int e = lane; e < D; e += 64) acc = fmaf(bf16_bits_to_f32(o[e]), bf16_bits_to_f32(g[e]), acc);
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) acc += __shfl_xor(acc, m);
-    if (lane == 0) p.dd[r] = acc;
-  }
-  const int64_t nth = (int64_t)gridDim.x * 256;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n_acc4; i += nth) {
-    reinterpret_cast<float4*>(p.dk_acc)[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-    reinterpret_cast<float4*>(p.dv_acc)[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (i >= p.n_btokens) return;
+  const BwdTokens k = load_scalar(p.btokens + i);
+  for (int j = lane; j < k.count; j += 64) {
+    p.btoks[(int64_t)k.dst + j] = k.row0 + j;
+    p.blims[(int64_t)k.dst + j] = min(k.lim0 + k.slope * j, k.lim_max);
   }
 }
 
@@ -119,8 +113,29 @@ __global__ __launch_bounds__(kThreads) void bwd_dq_kernel(BwdParams p) {
       bdo[kk] = as_bf16x8(valid ? load16(gp + kk * 16) : make_uint4(0, 0, 0, 0));
     }
   }
-  const float lse2 = valid ? p.lse[(int64_t)qrow * p.Hq + hq] * kLog2e : 0.f;
-  const float dcol = valid ? p.dd[(int64_t)qrow * p.Hq + hq] : 0.f;
+  const float lse = valid ? p.lse[(int64_t)qrow * p.Hq + hq] : 0.f;
+  const float lse2 = lse * kLog2e;
+  // D = dO . O of this lane's column (its lane half holds half of the dims),
+  // kept for the key-major kernel with -LSE / scale
+  float dcol = 0.f;
+  {
+    const uint16_t* op = static_cast<const uint16_t*>(p.o) + qoff + hf * 8;
+#pragma unroll
+    for (int kk = 0; kk < NKK; ++kk) {
+      const uint4 o4 = valid ? load16(op + kk * 16) : make_uint4(0, 0, 0, 0);
+      const uint32_t ow[4] = {o4.x, o4.y, o4.z, o4.w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        dcol = fmaf(__uint_as_float(ow[i] << 16), (float)bdo[kk][2 * i], dcol);
+        dcol = fmaf(__uint_as_float(ow[i] & 0xffff0000u), (float)bdo[kk][2 * i + 1], dcol);
+      }
+    }
+    dcol += __shfl_xor(dcol, 32);
+    if (valid && hf == 0) {
+      p.nd[(int64_t)qrow * p.Hq + hq] = -dcol;
+      p.nl[(int64_t)qrow * p.Hq + hq] = -lse / p.scale;
+    }
+  }
   const float sl2 = p.scale_log2;
 
   const uint16_t* Kg = static_cast<const uint16_t*>(p.k);
@@ -254,316 +269,438 @@ __global__ __launch_bounds__(kThreads) void bwd_dq_kernel(BwdParams p) {
 
 // ------------------------------------------------------------------ dK, dV
 
-template <int D>
+// 8 wavefronts, 4 groups of 32 keys by 2 halves of a step's 64 columns: each
+// forms S, P, dP and dS of its 32 x 32 block and adds its dV and dK, so that
+// no block value crosses wavefronts and a step needs one barrier; the two
+// column halves of a key group add up through LDS at the end.  Q and dO rows
+// come by direct global -> LDS loads, two steps ahead, into three stages.
+// Accumulators start at -LSE / scale and -D, which saves a subtraction each.
+//
+// What bounds it: a step's 32 products per wavefront are 2,048 cycles of each
+// matrix core (two wavefronts a SIMD), its fragment reads 288 KB of LDS, about
+// 2,500 cycles; it takes about 4,000.  More columns or keys per fragment read
+// would need more registers than two wavefronts a SIMD have (this one takes
+// 254, with a quarter of K in LDS).  Measured on one MI355X (d = 128, Hq 16,
+// Hkv 2), against wavefront pairs that passed P through LDS inside each
+// 32-column block: 8 ragged pages (43k tokens) 2,997 -> 1,870 us, one page of
+// 3,400 tokens 399 -> 118 us.  Of the latter, the sums of split runs: added
+// with fp32 atomics 336 us, through slots 118 + 8.6 for the reduction (atomics
+// on 194 pieces ran at about 45 G/s).
+// WIDE: Q or the list of limits is 4 GB or more, so places in them need 64 bits.
+template <int D, bool WIDE>
 __global__ __launch_bounds__(kThreads) void bwd_dkdv_kernel(BwdParams p) {
   constexpr int NKK = D / 16;
   constexpr int NDB = D / 32;
-  constexpr int CPR = D / 8;
-  // Q / dO blocks: 32 rows of D elements with swizzled 16-byte chunks
-  auto at = [&](int r, int c) { return r * D + (swizzled_chunk<CPR>(r, c) << 3); };
-
-  // Two stages: block i is computed from stage i%2 while block i+1 is stored
-  // into the other one (one barrier per block).
+  constexpr int CPR = D / 8;            // 16-byte chunks per row
+  constexpr int COLS = 64;              // columns per step
+  constexpr int RPI = 64 / CPR;         // rows per 1 KB load
+  constexpr int IPW = COLS / RPI / 8;   // 1 KB loads per wavefront, step and tensor
+  constexpr int kStages = 3;
   struct Stage {
-    uint16_t q[32 * D];  // Q rows (row = column of the block), swizzled chunks
-    uint16_t g[32 * D];  // dO rows
-    float ls[32];         // LSE * log2(e) per column
-    float dd[32];         // dO . O per column
-    int lm[32];           // keys of the item the column sees
+    uint16_t q[COLS * D];  // Q rows (row = column of the step), swizzled chunks
+    uint16_t g[COLS * D];  // dO rows
+    float nl[COLS];        // -LSE / scale per column
+    float nd[COLS];        // -dO . O per column
+    int lm[COLS];          // keys of the item the column sees
   };
-  __shared__ __attribute__((aligned(16))) Stage st[2];
-  // P of the block in bf16 per key group (wave & 3), as the dK wavefront's
-  // lanes hold it: [group][j][lane][8]
-  __shared__ __attribute__((aligned(16))) __bf16 Psh[4][2][64 * 8];
+  // the stages; at the end, the exchange of the column halves' sums
+  constexpr int kExchange = 2 * 4 * 2 * 64 * (int)sizeof(f32x16_t);
+  constexpr int kStageBytes = kStages * (int)sizeof(Stage);
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[kStageBytes > kExchange ? kStageBytes : kExchange];
+  Stage* st = reinterpret_cast<Stage*>(smem);
+  struct Columns {
+    uint32_t row[COLS];  // query row * Hq + head   (these three in bytes from
+    uint32_t val[COLS];  // the same                 the start of the array they
+    uint32_t lim[COLS];  // index of the limit       index, unless WIDE)
+  };
+  __shared__ Columns cols[4];  // of step t in list t % 4
+  auto at = [&](int r, int c) { return r * D + (swizzled_chunk<CPR>(r, c) << 3); };
+  // The lane index as a value the compiler takes for a new one: what each step
+  // derives from it (addresses) is formed in the step, a few operations, and
+  // holds no register through the products.
+  auto fresh_lane = [&]() __attribute__((always_inline)) -> int {
+    int x = threadIdx.x & 63;
+    asm volatile("" : "+v"(x));
+    return x;
+  };
 
-  const BwdRec b = p.bwd[blockIdx.x];
+  const BwdRec b = load_scalar(&p.bwd[blockIdx.x]);
   const int tid = threadIdx.x;
-  const int wave = tid >> 6, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
-  const bool kwave = wave >= 4;          // waves 4-7: dK; 0-3: dV
-  const int key = (wave & 3) * 32 + l32;  // this lane's key within the item
-  const int key_hi = (wave & 3) * 32 + 32;  // end of this wavefront's keys
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
+  const int kg = wave & 3, cb = wave >> 2;  // this wavefront's 32 keys and 32 columns of a step
+  const int key = kg * 32 + l32, key_hi = kg * 32 + 32;
+  const bool idle = kg * 32 >= b.n_keys;  // no key: stages and barriers only
   const int G = p.G, kvh = b.kvh;
   const int64_t Hkv = p.Hkv;
+  const int c_begin = b.col0, c_end = b.col0 + b.ncol;
 
   // B operands of S = Q K^T and dP = dO V^T: this lane's key, d = kk*16 + hf*8 ..
-  bf16x8_t bk[NKK], bv[NKK];
+  // At d = 128 the last kKL pieces of K wait in LDS (both column halves of a
+  // key group read the same), else the sums would not all fit the registers.
+  constexpr int kKL = D == 128 ? 4 : 0, NKR = NKK - kKL;
+  __shared__ __attribute__((aligned(16))) bf16x8_t Kl[4][kKL > 0 ? kKL : 1][64];
+  bf16x8_t bk[NKR], bv[NKK];
   {
     const int kc = key < b.n_keys ? key : b.n_keys - 1;
     const int64_t off = ((b.key_row0 + kc) * Hkv + kvh) * D + hf * 8;
 #pragma unroll
     for (int kk = 0; kk < NKK; ++kk) {
-      bk[kk] = as_bf16x8(load16(static_cast<const uint16_t*>(p.k) + off + kk * 16));
-      bv[kk] = as_bf16x8(kwave ? load16(static_cast<const uint16_t*>(p.v) + off + kk * 16) : make_uint4(0, 0, 0, 0));
+      bv[kk] = as_bf16x8(load16(static_cast<const uint16_t*>(p.v) + off + kk * 16));
+      const bf16x8_t x = as_bf16x8(load16(static_cast<const uint16_t*>(p.k) + off + kk * 16));
+      if (kk < NKR)
+        bk[kk] = x;
+      else if (cb == 0)
+        Kl[kg][kk - NKR][lane] = x;
     }
   }
 
-  // Staging geometry: thread -> (column, 16-byte chunk) of a 32-column block,
-  // columns fastest (16 lanes of a store write 16 rows of one chunk, which
-  // the swizzle spreads over all banks); with d = 64 the upper half of the
-  // threads repeats the lower half's loads and stores nothing.  Every thread
-  // also loads the per-column scalars of column tid % 32 (threads < 32 store
-  // them), so all threads issue the same loads and the compiler's load wait
-  // counts stay exact.
-  const int s_col = tid % 32, s_dc = (tid / 32) % CPR;
-  const bool s_on = tid < 32 * CPR;
-  const int c_end = b.col0 + b.ncol;
-  // Register sets [i % 2]: Q / dO pieces and column scalars of a block
-  // loaded two blocks ahead of its LDS store; the Q rows of its columns are
-  // fetched one block before that.
-  uint4 qr[2], gr[2];
-  float lr[2], dr[2];
-  int mr[2];
-  // Per set: Q row, token within the item and head of this thread's column
-  // (column tid % 32 of the block; past c_end: the last column, flagged).
-  int rq[2], tq[2], hq[2];
-  bool okq[2];
-  // fetch_rows visits the blocks in order, 32 columns apart: the column's
-  // (token, head) = (column / G, column % G) advances by (32 / G, 32 % G)
-  // with one carry, so no division runs per block.
-  int f_col = b.col0 + s_col, f_t = f_col / G, f_h = f_col % G;
-  const int t32 = 32 / G, h32 = 32 % G;
+  // Staging.  1 KB load i = wave*IPW + j of a tensor fills rows RPI*i ..
+  // RPI*i+RPI-1 of a stage; lane l fetches the chunk of row RPI*i + l/CPR whose
+  // place is l%CPR.  Row r of the step starting at column c is column c + r
+  // of the item: token (c + r) / G, head (c + r) % G.  One wavefront (7) works
+  // the columns out, a step before the others read them from LDS: c's own
+  // token and head advance in scalar registers, the quotient of the small
+  // rest is a multiplication (exact: x < 128, G <= 64).  Columns past c_end
+  // repeat the last one, whose Q, dO, LSE and D are finite, and count as
+  // seeing no key.
   const int t_end = (c_end - 1) / G, h_end = (c_end - 1) % G;
-  auto fetch_rows = [&](auto xc) __attribute__((always_inline)) {
-    constexpr int X = decltype(xc)::value;
-    const bool ok = f_col < c_end;
-    tq[X] = ok ? f_t : t_end;
-    hq[X] = ok ? f_h : h_end;
-    okq[X] = ok;
-    rq[X] = p.btoks[b.tok_begin + tq[X]];
-    f_col += 32;
-    f_t += t32;
-    f_h += h32;
+  const uint32_t inv_g = 65536u / (uint32_t)G + 1;
+  const int t64 = COLS / G, h64 = COLS % G;
+  int f_c = c_begin, f_t = c_begin / G, f_h = c_begin % G;  // next step to list
+  int l_c = f_c, l_t = f_t, l_h = f_h;              // the step fetched last
+  int32_t f_row = 0;                                // query row of its column `lane` (wavefront 7)
+  auto column = [&](int c, int t0, int h0, int& t, int& h) __attribute__((always_inline)) {
+    const uint32_t x = (uint32_t)(h0 + lane);
+    const uint32_t dt = (x * inv_g) >> 16;
+    const bool ok = c + lane < c_end;
+    t = ok ? t0 + (int)dt : t_end;
+    h = ok ? (int)(x - dt * (uint32_t)G) : h_end;
+  };
+  auto fetch_rows = [&]() __attribute__((always_inline)) {
+    int t, h;
+    column(f_c, f_t, f_h, t, h);
+    f_row = p.btoks[b.tok_begin + t];
+    l_c = f_c, l_t = f_t, l_h = f_h;
+    f_c += COLS;
+    f_t += t64;
+    f_h += h64;
     if (f_h >= G) {
       f_h -= G;
       ++f_t;
     }
   };
-  // A column past c_end carries the last column's (finite) Q, dO, LSE and
-  // D with a limit of 0: its P and dS are exactly 0, so it adds nothing.
-  auto load = [&](auto xc) __attribute__((always_inline)) {
-    constexpr int X = decltype(xc)::value;
-    const int64_t rh = (int64_t)rq[X] * p.Hq + kvh * G + hq[X];
-    const int64_t off = rh * D + s_dc * 8;
-    qr[X] = load16(static_cast<const uint16_t*>(p.q) + off);
-    gr[X] = load16(static_cast<const uint16_t*>(p.dout) + off);
-    lr[X] = p.lse[rh] * kLog2e;
-    dr[X] = p.dd[rh];
-    const int m = p.blims[b.lim_begin + tq[X]];
-    mr[X] = okq[X] ? m : 0;
+  auto list_rows = [&](int u) __attribute__((always_inline)) {  // the columns fetched last into list u
+    int t, h;
+    column(l_c, l_t, l_h, t, h);
+    const uint32_t row = (uint32_t)f_row * (uint32_t)p.Hq + (uint32_t)(kvh * G + h);
+    cols[u].row[lane] = WIDE ? row : row * (2 * D);
+    cols[u].val[lane] = WIDE ? row : row * 4;
+    cols[u].lim[lane] = WIDE ? (uint32_t)(b.lim_begin + t) : 4 * (uint32_t)(b.lim_begin + t);
   };
-  auto store = [&](auto xc, Stage& S) {
-    constexpr int X = decltype(xc)::value;
-    if (s_on) {
-      store16(&S.q[at(s_col, s_dc)], qr[X]);
-      store16(&S.g[at(s_col, s_dc)], gr[X]);
+  // Loads of the columns of list u into stage s: 2*IPW loads of 1 KB and one
+  // of 256 bytes per wavefront (wavefronts 3-7 repeat wavefront 2's).
+  auto load = [&](int u, int s) __attribute__((always_inline)) {
+    const int ln = fresh_lane();
+    const uint32_t r_off = wave * IPW * RPI + ln / CPR;
+    const uint32_t c_off = 16 * swizzled_chunk<CPR>(r_off, ln % CPR);
+    const uint32_t sq = tile::lds_addr(st[s].q) + wave * IPW * 1024, sg = tile::lds_addr(st[s].g) + wave * IPW * 1024;
+#pragma unroll
+    for (int j = 0; j < IPW; ++j) {
+      // the row of load 1 is 4 further on: its swizzle differs in bit 0
+      static_assert(IPW == 1 || (IPW == 2 && CPR == 16), "chunk of load 1");
+      const uint32_t row = cols[u].row[r_off + j * RPI];
+      const uint32_t c = c_off ^ (16 * j);
+      if constexpr (WIDE) {
+        const uint64_t off = (uint64_t)row * (2 * D) + c;
+        tile::dma16_v(static_cast<const char*>(p.q) + off, sq + j * 1024);
+        tile::dma16_v(static_cast<const char*>(p.dout) + off, sg + j * 1024);
+      } else {
+        tile::dma16(p.q, row + c, sq + j * 1024);
+        tile::dma16(p.dout, row + c, sg + j * 1024);
+      }
     }
-    if (tid < 32) {
-      S.ls[tid] = lr[X];
-      S.dd[tid] = dr[X];
-      S.lm[tid] = mr[X];
-    }
+    const void* base = wave == 0 ? (const void*)p.nl : wave == 1 ? (const void*)p.nd : (const void*)p.blims;
+    const uint32_t val = wave < 2 ? cols[u].val[ln] : cols[u].lim[ln];
+    const uint32_t to = tile::lds_addr(st[s].nl) + 256 * (wave < 2 ? wave : 2);
+    if constexpr (WIDE)
+      tile::dma4_v(static_cast<const uint32_t*>(base) + val, to);
+    else
+      tile::dma4(base, val, to);
   };
+  static_assert(offsetof(Stage, nd) == offsetof(Stage, nl) + 256 && offsetof(Stage, lm) == offsetof(Stage, nl) + 512, "scalars in a row");
 
-  f32x16_t acc[NDB];
+  f32x16_t dk[NDB], dv[NDB];
 #pragma unroll
   for (int db = 0; db < NDB; ++db)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[db][i] = 0.f;
+    for (int i = 0; i < 16; ++i) {
+      dk[db][i] = 0.f;
+      dv[db][i] = 0.f;
+    }
   const float sl2 = p.scale_log2;
 
-  // A operand d x columns (Q^T or dO^T) of d block db and column group j:
-  // lane (d, half) gets columns 16j + 4*half + {0..3} and + {8..11} of row
-  // d, with two transposing reads (lane r of a 16-lane group supplies row
-  // 16j + 4*half (+8) + r/4, elements d0 + 4*(r%4) .. +3).
-  const int tr_r = (lane & 15) >> 2, tr_c = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1), tr_o = 4 * (lane & 1);
-  auto trf = [&](const uint16_t* blk, int j, int db) __attribute__((always_inline)) -> bf16x8_t {
-    const int r0 = 16 * j + 4 * hf + tr_r, c = 4 * db + tr_c;
-    return tile::tr_pair(blk + at(r0, c) + tr_o, blk + at(r0 + 8, c) + tr_o);
-  };
+  // Fragment reads as LDS byte addresses: a per-lane base, and the d block by
+  // exclusive-or (a row is a multiple of 16 * CPR bytes and the swizzle is one),
+  // so that no register per block is held.
+  //   rows of Q or dO: row cb*32 + l32, d = kk*16 + hf*8 ..
+  //   transposed (Q^T, dO^T; d on M, columns on K) of d block db and column
+  //   group j: lane (d, half) gets columns 16j + 4*half + {0..3} and + {8..11}
+  //   of row d, with two transposing reads (lane r of a 16-lane group supplies
+  //   row 16j + 4*half (+8) + r/4, elements d0 + 4*(r%4) .. +3); 8 rows on,
+  //   bit 1 of the swizzle is the other one.
+  typedef __attribute__((address_space(3))) const bf16x8_t lds_frag;
+  typedef float f32x4_t __attribute__((ext_vector_type(4)));
+  typedef int i32x4_t __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) const f32x4_t lds_f4;
+  typedef __attribute__((address_space(3))) const i32x4_t lds_i4;
+  static_assert(sizeof(Stage) % 256 == 0, "exclusive-or on stage addresses");
 
-  // Block computation from one stage.  The dK wavefront of each key group
-  // (wave w + 4) computes S and P and hands P (bf16, in its score registers'
-  // layout) to the dV wavefront of the same keys (wave w) through LDS; the
-  // dV wavefront reads it after the block's first barrier, so S and the
-  // exponentials run once per key group.  Fragments of each product group
-  // are requested together before its matrix products.
-  auto compute = [&](const Stage& S) __attribute__((always_inline)) {
-    bf16x8_t fa[NKK];
-    bf16x8_t fb[2 * NDB];
-    float pr[16];
-    if (kwave) {
-      // S = Q K^T: columns on M, this wave's 32 keys on N.  Element i of a
-      // lane is column (i/4)*8 + hf*4 + i%4 of the block and key `key`.
-#pragma unroll
-      for (int kk = 0; kk < NKK; ++kk) fa[kk] = *reinterpret_cast<const bf16x8_t*>(&S.q[at(l32, 2 * kk + hf)]);
-      f32x16_t sc;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) sc[i] = 0.f;
-#pragma unroll
-      for (int kk = 0; kk < NKK; ++kk) sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[kk], bk[kk], sc, 0, 0, 0);
-      // P = exp(S - LSE), zero past each column's limit.  When every column
-      // of the block sees all 32 keys of this wavefront (limits are at most
-      // n_keys, so the keys are real), the mask is skipped.
-      float lv[16];
-      int mv[16];
+  // This wavefront's 32 columns of stage S against its 32 keys; `left`:
+  // columns of the step that exist.
+  auto compute = [&](const Stage& S, int left, auto&& between) __attribute__((always_inline)) {
+    // columns that see all of this wavefront's keys, one bit each
+    const int ln = fresh_lane(), n = ln & 31, hf = ln >> 5;
+    const uint64_t all = __ballot(S.lm[ln] >= key_hi && ln < left);
+    const bool full = (uint32_t)(all >> (32 * cb)) == 0xffffffffu;
+    const uint32_t base = tile::lds_addr(&S);
+    constexpr uint32_t kG = offsetof(Stage, g);
+    const int tr_r = cb * 32 + 4 * hf + ((ln & 15) >> 2), tr_c = 2 * ((ln >> 4) & 1) + ((ln & 3) >> 1);
+    uint32_t b_row = base + 2 * at(cb * 32 + n, hf), b_tr = base + 2 * (at(tr_r, tr_c) + 4 * (ln & 1));
+    // Before each product group: the block addresses are formed again (one
+    // operation each), not kept in 16 registers from the group before.
+    auto renew = [&]() __attribute__((always_inline)) { asm volatile("" : "+v"(b_row), "+v"(b_tr)); };
+    const uint32_t b_col = base + (uint32_t)offsetof(Stage, nl) + 4 * (cb * 32 + hf * 4);
+    // S - LSE / scale, columns on M, this wavefront's 32 keys on N: element i
+    // of a lane is column (i/4)*8 + hf*4 + i%4 and key `key`.
+    auto init = [&](uint32_t v) __attribute__((always_inline)) -> f32x16_t {
+      f32x16_t x;
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4) {
-        const int cb = q4 * 8 + hf * 4;  // columns cb .. cb+3 = elements 4*q4 .. 4*q4+3
-        const float4 l4 = *reinterpret_cast<const float4*>(&S.ls[cb]);
-        const int4 m4 = *reinterpret_cast<const int4*>(&S.lm[cb]);
-        lv[4 * q4] = l4.x, lv[4 * q4 + 1] = l4.y, lv[4 * q4 + 2] = l4.z, lv[4 * q4 + 3] = l4.w;
-        mv[4 * q4] = m4.x, mv[4 * q4 + 1] = m4.y, mv[4 * q4 + 2] = m4.z, mv[4 * q4 + 3] = m4.w;
+        const f32x4_t f = *(lds_f4*)(uintptr_t)(v + 32 * q4);
+        x[4 * q4] = f.x, x[4 * q4 + 1] = f.y, x[4 * q4 + 2] = f.z, x[4 * q4 + 3] = f.w;
       }
-      int mn = mv[0];
+      return x;
+    };
+    auto row = [&](uint32_t blk, int kk) __attribute__((always_inline)) -> bf16x8_t {
+      return *(lds_frag*)(uintptr_t)((b_row ^ (uint32_t)(kk << 5)) + blk);
+    };
+    auto trf = [&](uint32_t blk, int j, int db) __attribute__((always_inline)) -> bf16x8_t {
+      const uint32_t to = blk + j * 32 * D;
+      return tile::tr_pair_at((b_tr ^ (uint32_t)(db << 6)) + to, (b_tr ^ (uint32_t)((db << 6) | 32)) + to + 16 * D);
+    };
+    // The step's products in order: S (Q rows), dP (dO rows), dV (dO^T), dK
+    // (Q^T), with kPre fragment reads in flight throughout, also across the
+    // groups and while the first ones wait for `between` (the next loads).
+    // sched_barrier keeps the compiler from requesting more at once, which
+    // would not fit the registers beside the sums.
+    constexpr int kPre = 3, N1 = NKK, N2 = 2 * NKK, N3 = N2 + 2 * NDB, N4 = N3 + 2 * NDB;
+    auto frag = [&](auto ic) __attribute__((always_inline)) -> bf16x8_t {
+      constexpr int i = decltype(ic)::value;
+      if constexpr (i == N1 || i == N2 || i == N3) renew();
+      if constexpr (i < N1) return row(0, i);
+      else if constexpr (i < N2) return row(kG, i - N1);
+      else if constexpr (i < N3) return trf(kG, (i - N2) / NDB, (i - N2) % NDB);
+      else return trf(0, (i - N3) / NDB, (i - N3) % NDB);
+    };
+    bf16x8_t f[kPre];
+    tile::static_for<kPre>([&](auto ic) __attribute__((always_inline)) { f[decltype(ic)::value] = frag(ic); });
+    f32x16_t sc = init(b_col), dp;
+    between();
+    // P = exp(S - LSE), in place, between the dP products (the first
+    // two give the last S product time to land)
+    constexpr int kSlots = NKK - 1;
+    bf16x8_t pb[2], sb[2], kf[2];
+    tile::static_for<N4>([&](auto ic) __attribute__((always_inline)) {
+      constexpr int i = decltype(ic)::value;
+      if constexpr (i == N1) dp = init(b_col + 256);  // dP - D
+      if constexpr (i == N2) {
+        if (!full) {
+          tile::static_for<4>([&](auto qc) __attribute__((always_inline)) {
+            constexpr int q4 = decltype(qc)::value;
+            const int r0 = cb * 32 + q4 * 8 + hf * 4;
+            const i32x4_t m4 = *(lds_i4*)(uintptr_t)(b_col + 512 + 32 * q4);
+            const int mv[4] = {m4.x, m4.y, m4.z, m4.w};
 #pragma unroll
-      for (int i = 1; i < 16; ++i) mn = min(mn, mv[i]);
-      mn = min(mn, __shfl_xor(mn, 32));  // lanes l and l^32 hold the other 16 columns
-      if (__builtin_amdgcn_readfirstlane((int)(mn >= key_hi))) {
+            for (int e = 0; e < 4; ++e) sc[4 * q4 + e] = kg * 32 + n < mv[e] && r0 + e < left ? sc[4 * q4 + e] : 0.f;
+            __builtin_amdgcn_sched_barrier(0);
+          });
+        }
+        // four elements at a time, so that P and dP give way to the operands
+        tile::static_for<4>([&](auto gc) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) pr[i] = fast_exp2(fmaf(sc[i], sl2, -lv[i]));
-      } else {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) pr[i] = key < mv[i] ? fast_exp2(fmaf(sc[i], sl2, -lv[i])) : 0.f;
+          for (int e = 4 * decltype(gc)::value; e < 4 * decltype(gc)::value + 4; ++e) {
+            pb[e >> 3][e & 7] = (__bf16)sc[e];
+            sb[e >> 3][e & 7] = (__bf16)(sc[e] * dp[e]);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        });
       }
+      const bf16x8_t a = f[i % kPre];
+      bf16x8_t kb;
+      if constexpr (i >= NKR && i < N1) kb = kf[i % 2];
+      // dV^T += dO^T P, dK^T += Q^T dS: d on M (block db), keys on N, columns on K
+      // the LDS pieces of K, two ahead
+      if constexpr (i + 2 >= NKR && i + 2 < N1) kf[i % 2] = Kl[kg][i + 2 - NKR][ln];
+      if constexpr (i < NKR) sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bk[i], sc, 0, 0, 0);
+      else if constexpr (i < N1) sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, kb, sc, 0, 0, 0);
+      else if constexpr (i < N2) dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bv[i - N1], dp, 0, 0, 0);
+      else if constexpr (i < N3) dv[(i - N2) % NDB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb[(i - N2) / NDB], dv[(i - N2) % NDB], 0, 0, 0);
+      else dk[(i - N3) % NDB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, sb[(i - N3) / NDB], dk[(i - N3) % NDB], 0, 0, 0);
+      if constexpr (i + kPre < N4) f[i % kPre] = frag(std::integral_constant<int, i + kPre>{});
+      if constexpr (i > N1 && i < N2) {
+        constexpr int p0 = i - N1 - 1;
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        bf16x8_t pb;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) pb[e] = (__bf16)pr[8 * j + e];
-        *reinterpret_cast<bf16x8_t*>(&Psh[wave & 3][j][lane * 8]) = pb;
+        for (int e = 16 * p0 / kSlots; e < 16 * (p0 + 1) / kSlots; ++e) sc[e] = fast_exp2(sc[e] * sl2);
       }
-    } else {
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int db = 0; db < NDB; ++db)
-          fb[j * NDB + db] = trf(S.g, j, db);
-    }
-    __syncthreads();  // P of this block is in Psh
-    if (!kwave) {
-      // dV^T += dO^T P: d on M (block db), keys on N, columns on K
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const bf16x8_t pb = *reinterpret_cast<const bf16x8_t*>(&Psh[wave][j][lane * 8]);
-#pragma unroll
-        for (int db = 0; db < NDB; ++db)
-          acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j * NDB + db], pb, acc[db], 0, 0, 0);
-      }
-    } else {
-      // dP = dO V^T; dS = P (dP - D); dK^T += Q^T dS
-#pragma unroll
-      for (int kk = 0; kk < NKK; ++kk) fa[kk] = *reinterpret_cast<const bf16x8_t*>(&S.g[at(l32, 2 * kk + hf)]);
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int db = 0; db < NDB; ++db)
-          fb[j * NDB + db] = trf(S.q, j, db);
-      f32x16_t dP;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) dP[i] = 0.f;
-#pragma unroll
-      for (int kk = 0; kk < NKK; ++kk) dP = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[kk], bv[kk], dP, 0, 0, 0);
-      float dsv[16];
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const float4 d4 = *reinterpret_cast<const float4*>(&S.dd[q4 * 8 + hf * 4]);
-        const float dv[4] = {d4.x, d4.y, d4.z, d4.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) dsv[4 * q4 + e] = pr[4 * q4 + e] * (dP[4 * q4 + e] - dv[e]);
-      }
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        bf16x8_t sb;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) sb[e] = (__bf16)dsv[8 * j + e];
-#pragma unroll
-        for (int db = 0; db < NDB; ++db)
-          acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j * NDB + db], sb, acc[db], 0, 0, 0);
-      }
-    }
+      __builtin_amdgcn_sched_barrier(0);
+    });
   };
 
-  // Block i is computed from stage i % 2 and its pieces sit in register set
-  // i % 2 until stored (at step i-1); step i stores block i+1, loads block
-  // i+2 into set i % 2 and fetches the rows of block i+3 into row set
-  // (i+1) % 2.
-  using Set0 = std::integral_constant<int, 0>;
-  using Set1 = std::integral_constant<int, 1>;
-  fetch_rows(Set0{});  // block 0
-  load(Set0{});
-  fetch_rows(Set1{});  // block 1
-  load(Set1{});
-  store(Set0{}, st[0]);
-  fetch_rows(Set0{});  // block 2
-  __syncthreads();
-  auto step = [&](auto xc, int c0) {
-    constexpr int X = decltype(xc)::value;
-    using Y = std::integral_constant<int, X ^ 1>;
-    compute(st[X]);
-    if (c0 + 32 < c_end) store(Y{}, st[X ^ 1]);  // that stage was last read before the previous barrier
-    load(xc);           // block i+2
-    fetch_rows(Y{});    // block i+3
-    __syncthreads();
-  };
-  for (int c0 = b.col0;;) {
-    step(Set0{}, c0);
-    c0 += 32;
-    if (c0 >= c_end) break;
-    step(Set1{}, c0);
-    c0 += 32;
-    if (c0 >= c_end) break;
+  // Step t computes stage t % 3, loaded at step t-2, and loads the columns of
+  // step t+2 into the stage of step t-1, which every wavefront has read
+  // before this step's barrier; their list was written at step t-1, and the
+  // list of step t+3 is written now, where step t-1's was.  Before the barrier
+  // each wavefront waits for its own loads of step t (at most the 2*IPW+1 of
+  // step t+1 may still be in flight) and wavefront 7 for its list's stores.
+  const int n_steps = (c_end - c_begin + COLS - 1) / COLS;
+  if (wave == 7) {
+#pragma unroll
+    for (int u = 0; u < 3; ++u) {
+      fetch_rows();
+      list_rows(u);
+    }
+    fetch_rows();
   }
+  __syncthreads();
+  load(0, 0);
+  load(1, 1);
+  int s = 0, left = c_end - c_begin;
+  for (int t = 0; t < n_steps; ++t, left -= COLS) {
+    tile::wait_vm<2 * IPW + 1>();
+    if (wave == 7) __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+    tile::bar();
+    auto feed = [&]() __attribute__((always_inline)) {
+      load((t + 2) & 3, s == 0 ? 2 : s - 1);
+      if (wave == 7) {
+        list_rows((t + 3) & 3);
+        fetch_rows();
+      }
+    };
+    if (idle)
+      feed();
+    else
+      compute(st[s], left, feed);
+    s = s == 2 ? 0 : s + 1;
+  }
+  __builtin_amdgcn_s_waitcnt(0);
+  tile::bar();  // no load in flight, no stage in use
 
+  // The two column halves of a key group add up through LDS: wavefronts 0-3
+  // end with dK of their keys, wavefronts 4-7 with dV, 64 dims at a time.
+  f32x16_t* xch = reinterpret_cast<f32x16_t*>(smem);  // [tensor][kg][db % 2][lane]
+#pragma unroll
+  for (int h = 0; h < NDB / 2 + NDB % 2; ++h) {
+    if (h) __syncthreads();
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+      if (2 * h + x < NDB) xch[((cb * 4 + kg) * 2 + x) * 64 + lane] = cb ? dk[2 * h + x] : dv[2 * h + x];
+    __syncthreads();
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+      if (2 * h + x < NDB) {
+        const f32x16_t o = xch[(((cb ^ 1) * 4 + kg) * 2 + x) * 64 + lane];
+        if (cb)
+          dv[2 * h + x] += o;
+        else
+          dk[2 * h + x] += o;
+      }
+  }
   if (key >= b.n_keys) return;
-  // acc[db] element i: d = db*32 + (i/4)*8 + hf*4 + i%4, key `key`.  An item
-  // that holds all of its key run's columns stores its rows; the pieces of a
-  // split run add into them (rows start at zero).
-  float* dst = (kwave ? p.dk_acc : p.dv_acc) + ((b.key_row0 + key) * Hkv + kvh) * D;
-  const float sc = kwave ? p.scale : 1.f;
-  if (b.col0 == 0 && b.ncol == b.ntok * G) {
+  // element i of block db: d = db*32 + (i/4)*8 + hf*4 + i%4, key `key`.  An item
+  // that holds all of its key run's columns writes its rows, a piece of a
+  // split run its slot's (the sums follow in bwd_reduce_kernel).
+  const float scl = cb ? 1.f : p.scale;
+  const int32_t slot = b.cost;
+  if (slot < 0) {
+    uint16_t* dst = static_cast<uint16_t*>(cb ? p.dv : p.dk) + ((b.key_row0 + key) * Hkv + kvh) * D;
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
-      for (int i4 = 0; i4 < 4; ++i4)
-        *reinterpret_cast<float4*>(dst + db * 32 + i4 * 8 + hf * 4) =
-            make_float4(acc[db][4 * i4] * sc, acc[db][4 * i4 + 1] * sc, acc[db][4 * i4 + 2] * sc,
-                        acc[db][4 * i4 + 3] * sc);
+      for (int i4 = 0; i4 < 4; ++i4) {
+        float x[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = (cb ? dv[db][4 * i4 + e] : dk[db][4 * i4 + e]) * scl;
+        uint2 pk;
+        pk.x = (uint32_t)f32_to_bf16_bits(x[0]) | ((uint32_t)f32_to_bf16_bits(x[1]) << 16);
+        pk.y = (uint32_t)f32_to_bf16_bits(x[2]) | ((uint32_t)f32_to_bf16_bits(x[3]) << 16);
+        *reinterpret_cast<uint2*>(dst + db * 32 + i4 * 8 + hf * 4) = pk;
+      }
   } else {
+    float* dst = p.part + (((int64_t)slot * 2 + cb) * kBwdKeys + key) * D;
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) atomicAdd(dst + db * 32 + (i >> 2) * 8 + hf * 4 + (i & 3), acc[db][i] * sc);
+      for (int i4 = 0; i4 < 4; ++i4) {
+        float x[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = (cb ? dv[db][4 * i4 + e] : dk[db][4 * i4 + e]) * scl;
+        *reinterpret_cast<float4*>(dst + db * 32 + i4 * 8 + hf * 4) = make_float4(x[0], x[1], x[2], x[3]);
+      }
   }
 }
 
-// ------------------------------------------------------------------ finalize
+// ------------------------------------------------------------------ sums
 
-__global__ __launch_bounds__(256) void bwd_finalize_kernel(BwdParams p, int64_t n4) {
-  const int64_t nth = (int64_t)gridDim.x * 256;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += nth) {
-    const float4 a = reinterpret_cast<const float4*>(p.dk_acc)[i];
-    const float4 c = reinterpret_cast<const float4*>(p.dv_acc)[i];
-    uint2 ka, va;
-    ka.x = (uint32_t)f32_to_bf16_bits(a.x) | ((uint32_t)f32_to_bf16_bits(a.y) << 16);
-    ka.y = (uint32_t)f32_to_bf16_bits(a.z) | ((uint32_t)f32_to_bf16_bits(a.w) << 16);
-    va.x = (uint32_t)f32_to_bf16_bits(c.x) | ((uint32_t)f32_to_bf16_bits(c.y) << 16);
-    va.y = (uint32_t)f32_to_bf16_bits(c.z) | ((uint32_t)f32_to_bf16_bits(c.w) << 16);
-    reinterpret_cast<uint2*>(p.dk)[i] = ka;
-    reinterpret_cast<uint2*>(p.dv)[i] = va;
+// dK and dV rows of split key runs: the pieces' sums added in their order
+// (so results do not depend on scheduling) and rounded to bf16 (nearest
+// even); and zero rows where no query sees a key.  One workgroup per 16 rows
+// of a record: a copy, 16 bytes a lane, a piece's loads in flight together.
+template <int D>
+__global__ __launch_bounds__(256) void bwd_reduce_kernel(BwdParams p) {
+  constexpr int kRows = 16, kParts = kBwdKeys / kRows, Q = D / 4;
+  const BwdReduce r = load_scalar(p.breduce + blockIdx.x / kParts);
+  const int k0 = (blockIdx.x % kParts) * kRows;
+  if (k0 >= r.n_keys) return;
+  const int rows = min(kRows, r.n_keys - k0);
+  if (r.n_slots == 0) {
+    // rows k0 .. of all heads, contiguous
+    uint2* dk = reinterpret_cast<uint2*>(p.dk) + (r.row0 + k0) * p.Hkv * Q;
+    uint2* dv = reinterpret_cast<uint2*>(p.dv) + (r.row0 + k0) * p.Hkv * Q;
+    for (int64_t i = threadIdx.x; i < (int64_t)rows * p.Hkv * Q; i += 256) dk[i] = dv[i] = make_uint2(0, 0);
+    return;
   }
+  for (int i = threadIdx.x; i < 2 * rows * Q; i += 256) {
+    const int t = i / (rows * Q), e = i % (rows * Q), key = k0 + e / Q, c = e % Q;
+    const float4* src = reinterpret_cast<const float4*>(p.part) + (((int64_t)r.slot0 * 2 + t) * kBwdKeys + key) * Q + c;
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 4
+    for (int s = 0; s < r.n_slots; ++s) {
+      const float4 x = src[(int64_t)s * 2 * kBwdKeys * Q];
+      a.x += x.x, a.y += x.y, a.z += x.z, a.w += x.w;
+    }
+    uint2 pk;
+    pk.x = (uint32_t)f32_to_bf16_bits(a.x) | ((uint32_t)f32_to_bf16_bits(a.y) << 16);
+    pk.y = (uint32_t)f32_to_bf16_bits(a.z) | ((uint32_t)f32_to_bf16_bits(a.w) << 16);
+    uint16_t* dst = static_cast<uint16_t*>(t ? p.dv : p.dk) + ((r.row0 + key) * p.Hkv + r.kvh) * D;
+    reinterpret_cast<uint2*>(dst)[c] = pk;
+  }
+}
+
+template <int D>
+void launch_dkdv(const BwdParams& p, int n_bwd, hipStream_t stream) {
+  if (std::max(p.n_q * p.Hq * D * 2, p.n_btok * 4) < (int64_t)1 << 32)
+    hipLaunchKernelGGL((bwd_dkdv_kernel<D, false>), dim3(n_bwd), dim3(kThreads), 0, stream, p);
+  else
+    hipLaunchKernelGGL((bwd_dkdv_kernel<D, true>), dim3(n_bwd), dim3(kThreads), 0, stream, p);
 }
 
 }  // namespace
 
 hipError_t launch_tree_attn_bwd(const BwdParams& p, int n_work, int n_bwd, int D, hipStream_t stream) {
-  const int64_t n_rows = p.n_q * p.Hq;
-  const int64_t n_acc4 = p.T * p.Hkv * D / 4;
-  const int64_t want = (std::max(n_rows / 4, n_acc4 / 256) + 1);
-  const dim3 prep_grid((unsigned)std::min<int64_t>(want, 4096)), blk256(256), blk512(kThreads);
-  if (D == 64)
-    hipLaunchKernelGGL((bwd_prep_kernel<64>), prep_grid, blk256, 0, stream, p, n_rows, n_acc4);
-  else
-    hipLaunchKernelGGL((bwd_prep_kernel<128>), prep_grid, blk256, 0, stream, p, n_rows, n_acc4);
+  const dim3 blk256(256), blk512(kThreads);
+  if (p.n_btokens > 0)
+    hipLaunchKernelGGL(bwd_tokens_kernel, dim3((unsigned)((p.n_btokens + 3) / 4)), blk256, 0, stream, p);
   if (n_work > 0) {
     if (D == 64)
       hipLaunchKernelGGL((bwd_dq_kernel<64>), dim3(n_work), blk512, 0, stream, p);
@@ -572,13 +709,16 @@ hipError_t launch_tree_attn_bwd(const BwdParams& p, int n_work, int n_bwd, int D
   }
   if (n_bwd > 0) {
     if (D == 64)
-      hipLaunchKernelGGL((bwd_dkdv_kernel<64>), dim3(n_bwd), blk512, 0, stream, p);
+      launch_dkdv<64>(p, n_bwd, stream);
     else
-      hipLaunchKernelGGL((bwd_dkdv_kernel<128>), dim3(n_bwd), blk512, 0, stream, p);
+      launch_dkdv<128>(p, n_bwd, stream);
   }
-  if (n_acc4 > 0) {
-    const dim3 fin_grid((unsigned)std::min<int64_t>(n_acc4 / 256 + 1, 4096));
-    hipLaunchKernelGGL(bwd_finalize_kernel, fin_grid, blk256, 0, stream, p, n_acc4);
+  if (p.n_breduce > 0) {
+    const dim3 grid((unsigned)p.n_breduce * (kBwdKeys / 16));
+    if (D == 64)
+      hipLaunchKernelGGL((bwd_reduce_kernel<64>), grid, blk256, 0, stream, p);
+    else
+      hipLaunchKernelGGL((bwd_reduce_kernel<128>), grid, blk256, 0, stream, p);
   }
   return hipGetLastError();
 }

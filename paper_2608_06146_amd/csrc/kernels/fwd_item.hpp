@@ -119,6 +119,13 @@ __device__ __forceinline__ void dma16_nt(const void* base, uint32_t voff, uint32
 __device__ __forceinline__ void dma4(const void* base, uint32_t voff, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory", "m0");
 }
+// The same with a 64-bit address per lane.
+__device__ __forceinline__ void dma16_v(const void* a, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(a) : "memory", "m0");
+}
+__device__ __forceinline__ void dma4_v(const void* a, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(lds), "v"(a) : "memory", "m0");
+}
 #pragma clang diagnostic pop
 
 template <int D, bool PAGED>

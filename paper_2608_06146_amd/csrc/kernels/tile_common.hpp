@@ -35,6 +35,13 @@ __device__ __forceinline__ RangeRec uniform_range(RangeRec r) {
 // Two transposing LDS reads (4 bf16 each) joined into one 8-element MFMA
 // operand: elements 0-3 from the read at lo, 4-7 from the read at hi.
 typedef short i16x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ bf16x8_t tr_pair_at(uint32_t lo, uint32_t hi) {  // LDS byte addresses
+  typedef __attribute__((address_space(3))) i16x4_t lds_i16x4;
+  const i16x4_t a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(uintptr_t)lo);
+  const i16x4_t b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(uintptr_t)hi);
+  const short __attribute__((ext_vector_type(8))) ab = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+  return __builtin_bit_cast(bf16x8_t, ab);
+}
 __device__ __forceinline__ bf16x8_t tr_pair(const uint16_t* lo, const uint16_t* hi) {
   typedef __attribute__((address_space(3))) i16x4_t lds_i16x4;
   const i16x4_t a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(const_cast<uint16_t*>(lo)));

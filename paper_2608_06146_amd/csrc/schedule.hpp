@@ -28,6 +28,19 @@ constexpr int kBwdKeys = 128;     // keys of a backward key-major item (4 x 32)
 constexpr int kMaxItemKeys = 8192;  // decode: keys of a chunk (item) at most
 constexpr int kMaxItemTiles = kMaxItemKeys / kTileKeys;  // tiles of a paged tile item at most
 
+// Backward schedule records that only the device reads.  A BwdRec on the
+// device holds in `cost` the partial slot its item writes (-1: the item has
+// all columns of its key run and writes the run's dK / dV rows).
+struct BwdTokens {  // tokens dst .. dst+count-1 of the items' token lists:
+  int32_t dst, row0, count;  // query row row0 + i,
+  int32_t lim0, slope, lim_max;  // limit min(lim0 + slope * i, lim_max)
+};
+struct BwdReduce {  // n_slots > 0: rows = sum of the slots; 0: n_keys rows of every head are zero
+  int64_t row0;
+  int32_t n_keys, kvh, slot0, n_slots;
+};
+static_assert(sizeof(BwdTokens) == 24 && sizeof(BwdReduce) == 24, "device records");
+
 // Everything a tile kernel needs.  Pointers are device pointers.
 struct TileParams {
   const void* q;          // [n_q, Hq, D]
@@ -57,17 +70,20 @@ struct BwdParams {
   void* dq;          // [n_q, Hq, D]
   void* dk;          // [T, Hkv, D]
   void* dv;
-  float* dd;         // workspace [n_q, Hq]: sum_d dout * o
-  float* dk_acc;     // workspace [T, Hkv, D] fp32
-  float* dv_acc;
+  float* nd;         // workspace [n_q, Hq]: -sum_d dout * o
+  float* nl;         // workspace [n_q, Hq]: -lse / scale
+  float* part;       // workspace [slots][2: dK, dV][kBwdKeys][D] fp32: sums of the pieces of split key runs
   const WorkRec* work;  // the forward's query-major items (dQ)
   const RangeRec* ranges;
   const int32_t* lims;
   const int32_t* toks;
   const BwdRec* bwd;    // key-major items (dK, dV)
-  const int32_t* btoks;
-  const int32_t* blims;
-  int64_t n_q, T;
+  int32_t* btoks;       // workspace, written from btokens
+  int32_t* blims;
+  const BwdTokens* btokens;
+  const BwdReduce* breduce;
+  int64_t n_q, T, n_btok;
+  int32_t n_btokens, n_breduce;
   int32_t Hq, Hkv, G;
   float scale, scale_log2;
 };
