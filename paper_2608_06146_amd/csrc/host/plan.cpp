@@ -450,7 +450,7 @@ struct BwdRun {
 // 32-column blocks of the longest piece a key run is cut into.  Items run one
 // per compute unit, longest first; a piece beyond the first costs its start
 // and end, about four 64-column steps, and its sums go through memory.  Few
-// candidates between a sixth of a unit's share of all blocks and no cut are
+// candidates between a fifth of a unit's share of all blocks and no cut are
 // tried on the greedy assignment the dispatch makes of them, and the one with
 // the earliest end is taken (the longest on a tie); never under 64 blocks.
 int64_t bwd_piece_blocks(const std::vector<BwdRun>& runs, int64_t G, int64_t Hkv, int64_t units) {
@@ -464,7 +464,7 @@ int64_t bwd_piece_blocks(const std::vector<BwdRun>& runs, int64_t G, int64_t Hkv
   if (runs.size() > 20000) return std::max<int64_t>(64, share);  // many more runs than units: already even
   int64_t best = 0, best_end = std::numeric_limits<int64_t>::max();
   std::vector<int64_t> cost, load;
-  for (const double f : {1e9, 2.0, 1.5, 1.2, 1.0, 0.85, 0.7, 0.6, 0.5, 0.42, 0.35, 0.3, 0.25, 0.2, 0.167}) {
+  for (const double f : {1e9, 1.5, 1.2, 0.85, 0.6, 0.42, 0.3, 0.2}) {
     const int64_t cap = std::max<int64_t>(64, f > 1e6 ? longest : (int64_t)(f * (double)share));
     cost.clear();
     int64_t split = 0;

@@ -76,124 +76,121 @@ __global__ __launch_bounds__(256) void bwd_tokens_kernel(BwdParams p) {
 
 // ------------------------------------------------------------------ dQ
 
+// 8 wavefronts of 32 columns.  A wavefront takes a 64-key tile in two halves:
+// the products of one run beside the vector work of the other.  K and V come
+// by direct global -> LDS loads into three stages, one barrier a tile.
 template <int D>
 __global__ __launch_bounds__(kThreads) void bwd_dq_kernel(BwdParams p) {
   constexpr int KT = kTileKeys;  // 64 keys per tile
   constexpr int NKK = D / 16;
   constexpr int NDB = D / 32;
-  constexpr int CPR = D / 8;
-  constexpr int KPT = KT * CPR / kThreads;  // row pieces per thread (2 or 1)
-
-  // K and V tiles: KT rows of D elements with swizzled 16-byte chunks (see
-  // swizzled_chunk), read by rows for S and dP and transposed (K^T) for dQ.
-  __shared__ __attribute__((aligned(16))) uint16_t Ks[KT * D];
-  __shared__ __attribute__((aligned(16))) uint16_t Vs[KT * D];
+  constexpr int CPR = D / 8;              // 16-byte chunks per row
+  constexpr int RPI = 64 / CPR;           // rows per 1 KB load
+  constexpr int IPW = KT / RPI / 8;       // 1 KB loads per wavefront, tile and tensor
+  constexpr int kStages = 3, kTile = KT * D;
+  // K and V stages: KT rows of D elements with swizzled 16-byte chunks, read
+  // by rows for S and dP and transposed (K^T) for dQ.
+  __shared__ __attribute__((aligned(1024))) uint16_t sm[kStages][2][kTile];
   auto at = [&](int r, int c) { return r * D + (swizzled_chunk<CPR>(r, c) << 3); };
 
-  const WorkRec w = p.work[blockIdx.x];
+  const WorkRec w = load_scalar(&p.work[blockIdx.x]);
   if (w.rng_count <= 0) return;
   const int tid = threadIdx.x;
-  const int wave = tid >> 6, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
   const int G = p.G, kvh = w.kvh;
-  const int64_t Hkv = p.Hkv;
+
   const int col = wave * 32 + l32;
   const int tok = col / G;
   const bool valid = tok < w.ntok;
   const int32_t qrow = valid ? p.toks[w.tok_begin + tok] : 0;
-  const int32_t hq = kvh * G + (col - tok * G);
-  const int64_t qoff = ((int64_t)qrow * p.Hq + hq) * D;
-
+  const int64_t row = (int64_t)qrow * p.Hq + kvh * G + (valid ? col - tok * G : 0);
   bf16x8_t bq[NKK], bdo[NKK];
+  float lse2, dcol;
   {
-    const uint16_t* qp = static_cast<const uint16_t*>(p.q) + qoff + hf * 8;
-    const uint16_t* gp = static_cast<const uint16_t*>(p.dout) + qoff + hf * 8;
+    const uint16_t* qp = static_cast<const uint16_t*>(p.q) + row * D + hf * 8;
+    const uint16_t* gp = static_cast<const uint16_t*>(p.dout) + row * D + hf * 8;
+    const uint16_t* op = static_cast<const uint16_t*>(p.o) + row * D + hf * 8;
+    // D = dO . O (a lane half holds half of the dims), kept for the key-major
+    // kernel with -LSE / scale
+    float dd = 0.f;
 #pragma unroll
     for (int kk = 0; kk < NKK; ++kk) {
       bq[kk] = as_bf16x8(valid ? load16(qp + kk * 16) : make_uint4(0, 0, 0, 0));
       bdo[kk] = as_bf16x8(valid ? load16(gp + kk * 16) : make_uint4(0, 0, 0, 0));
-    }
-  }
-  const float lse = valid ? p.lse[(int64_t)qrow * p.Hq + hq] : 0.f;
-  const float lse2 = lse * kLog2e;
-  // D = dO . O of this lane's column (its lane half holds half of the dims),
-  // kept for the key-major kernel with -LSE / scale
-  float dcol = 0.f;
-  {
-    const uint16_t* op = static_cast<const uint16_t*>(p.o) + qoff + hf * 8;
-#pragma unroll
-    for (int kk = 0; kk < NKK; ++kk) {
       const uint4 o4 = valid ? load16(op + kk * 16) : make_uint4(0, 0, 0, 0);
       const uint32_t ow[4] = {o4.x, o4.y, o4.z, o4.w};
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        dcol = fmaf(__uint_as_float(ow[i] << 16), (float)bdo[kk][2 * i], dcol);
-        dcol = fmaf(__uint_as_float(ow[i] & 0xffff0000u), (float)bdo[kk][2 * i + 1], dcol);
+        dd = fmaf(__uint_as_float(ow[i] << 16), (float)bdo[kk][2 * i], dd);
+        dd = fmaf(__uint_as_float(ow[i] & 0xffff0000u), (float)bdo[kk][2 * i + 1], dd);
       }
     }
-    dcol += __shfl_xor(dcol, 32);
+    dcol = dd + __shfl_xor(dd, 32);
+    const float lse = valid ? p.lse[row] : 0.f;
+    lse2 = lse * kLog2e;
     if (valid && hf == 0) {
-      p.nd[(int64_t)qrow * p.Hq + hq] = -dcol;
-      p.nl[(int64_t)qrow * p.Hq + hq] = -lse / p.scale;
+      p.nd[row] = -dcol;
+      p.nl[row] = -lse / p.scale;
     }
   }
   const float sl2 = p.scale_log2;
 
-  const uint16_t* Kg = static_cast<const uint16_t*>(p.k);
-  const uint16_t* Vg = static_cast<const uint16_t*>(p.v);
-  // row pieces (key, 16-byte chunk)
-  int r_key[KPT], r_dc[KPT];
-#pragma unroll
-  for (int i = 0; i < KPT; ++i) {
-    const int u = tid + kThreads * i;
-    r_key[i] = u / CPR;
-    r_dc[i] = u % CPR;
-  }
-
+  int n_tiles = 0;
+  for (int r = 0; r < w.rng_count; ++r)
+    n_tiles += (load_scalar(&p.ranges[w.rng_begin + r]).n_keys + KT - 1) / KT;
   struct Cursor {
     int ri, kt;
     RangeRec R;
-    int ok, unused;
   };
-  auto advance = [&](Cursor& c) {
+  auto advance = [&](Cursor& c) {  // past the last tile it stays on a valid one
     if (++c.kt * KT >= c.R.n_keys) {
       c.kt = 0;
-      if (++c.ri < w.rng_count)
-        c.R = p.ranges[w.rng_begin + c.ri];
-      else
-        c.ok = 0;
+      if (++c.ri < w.rng_count) c.R = load_scalar(&p.ranges[w.rng_begin + c.ri]);
     }
   };
-  uint4 kr[KPT], vr[KPT];
-  // Tile loads: rows past the range end repeat its last row (finite values
-  // whose scores the mask removes).
-  auto load = [&](const Cursor& c) {
+  // This wavefront's loads of the tile at cursor c into stage s.  Rows past
+  // the range's end repeat its last row (finite values whose scores the mask
+  // removes).
+  const uint32_t HD = (uint32_t)p.Hkv * D;
+  const int ld_r = wave * IPW * RPI + lane / CPR;
+  auto load = [&](const Cursor& c, int s) __attribute__((always_inline)) {
     const int kbase = c.kt * KT, last = c.R.n_keys - 1 - kbase;
-    const int64_t row0 = c.R.kv_start + kbase;
+    const int64_t first = tile::uniform64(c.R.kv_start + kbase) * (int64_t)HD;
+    const uint16_t* kp = static_cast<const uint16_t*>(p.k) + first;
+    const uint16_t* vp = static_cast<const uint16_t*>(p.v) + first;
+    const uint32_t sk = tile::lds_addr(sm[s][0]) + wave * IPW * 1024, sv = tile::lds_addr(sm[s][1]) + wave * IPW * 1024;
 #pragma unroll
-    for (int i = 0; i < KPT; ++i) {
-      const int kc = r_key[i] <= last ? r_key[i] : last;
-      const int64_t off = ((row0 + kc) * Hkv + kvh) * D + r_dc[i] * 8;
-      kr[i] = load16(Kg + off);
-      vr[i] = load16(Vg + off);
+    for (int j = 0; j < IPW; ++j) {
+      const int r = ld_r + j * RPI;
+      const uint32_t off = 2 * (__umul24((uint32_t)min(r, last), HD) + (uint32_t)kvh * D + 8 * swizzled_chunk<CPR>(r, lane % CPR));
+      tile::dma16(kp, off, sk + j * 1024);
+      tile::dma16(vp, off, sv + j * 1024);
     }
-  };
-  auto store = [&]() {
-#pragma unroll
-    for (int i = 0; i < KPT; ++i) {
-      store16(&Ks[at(r_key[i], r_dc[i])], kr[i]);
-      store16(&Vs[at(r_key[i], r_dc[i])], vr[i]);
-    }
-  };
-  // K^T operand of dQ^T += K^T dS^T for keys mb*32 + 16j + 4*half + {0..3},
-  // {8..11} and d block db: two transposing reads (lane r of a 16-lane group
-  // supplies key row .. + r/4, elements d0 + 4*(r%4) .. +3)
-  const int tr_r = (lane & 15) >> 2, tr_c = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1), tr_o = 4 * (lane & 1);
-  auto ktf = [&](int mb, int j, int db) __attribute__((always_inline)) -> bf16x8_t {
-    const int r0 = mb * 32 + 16 * j + 4 * hf + tr_r, c = 4 * db + tr_c;
-    return tile::tr_pair(Ks + at(r0, c) + tr_o, Ks + at(r0 + 8, c) + tr_o);
   };
   auto lim_of = [&](const RangeRec& R) -> int {
     return R.lim_off < 0 ? R.n_keys : (valid ? p.lims[R.lim_off + tok] : 0);
+  };
+
+  // Fragment addresses (bytes): rows of K or V: row mb*32 + l32, d = kk*16 +
+  // hf*8 ..; K^T (d on M, keys on K) for keys mb*32 + 16j + 4*half + {0..3},
+  // {8..11} of d block db: two transposing reads (lane r of a 16-lane group
+  // supplies key row .. + r/4, elements d0 + 4*(r%4) .. +3).
+  typedef __attribute__((address_space(3))) const bf16x8_t lds_frag;
+  const int tr_r = 4 * hf + ((lane & 15) >> 2), tr_c = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
+  const uint32_t a_row = 2 * at(l32, hf), a_tr = 2 * (at(tr_r, tr_c) + 4 * (lane & 1));
+  const uint32_t lds0 = tile::lds_addr(sm);
+  constexpr uint32_t kV = 2 * kTile;  // V tile after the K tile of a stage
+  // A base that the compiler takes for a new value: the block addresses are
+  // formed for each product group (one operation each), not kept.
+  auto base = [&](uint32_t st, uint32_t a) __attribute__((always_inline)) -> uint32_t {
+    uint32_t x = st + a;
+    asm volatile("" : "+v"(x));
+    return x;
+  };
+  auto ktf = [&](uint32_t b, int mb, int j, int db) __attribute__((always_inline)) -> bf16x8_t {
+    const uint32_t to = mb * 64 * D + j * 32 * D;
+    return tile::tr_pair_at((b ^ (uint32_t)(db << 6)) + to, (b ^ (uint32_t)((db << 6) | 32)) + to + 16 * D);
   };
 
   f32x16_t acc[NDB];
@@ -201,69 +198,121 @@ __global__ __launch_bounds__(kThreads) void bwd_dq_kernel(BwdParams p) {
   for (int db = 0; db < NDB; ++db)
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[db][i] = 0.f;
+  // One tile, in stage st: S and dP of half 0; those of half 1 beside the dS
+  // of half 0; dQ of half 0 beside the dS of half 1; dQ of half 1.  Element i
+  // of half mb is key mb*32 + (i/4)*8 + hf*4 + i%4 of the tile, visible below
+  // rel (relative to the tile and the lane half).
+  auto tile_step = [&](uint32_t st, bool partial, int rel) __attribute__((always_inline)) {
+    constexpr int kPre = 4, NA = 2 * NKK, NQ = 2 * NDB;
+    f32x16_t S[2], dP[2];
+    bf16x8_t ds[2][2];
+    float x[8];
+    // S and dP products of half mb, hook(i) after product i
+    auto scores = [&](auto mbc, auto&& hook) __attribute__((always_inline)) {
+      constexpr int mb = decltype(mbc)::value;
+      const uint32_t b = base(st, a_row);
+      auto frag = [&](int i) __attribute__((always_inline)) -> bf16x8_t {
+        return *(lds_frag*)(uintptr_t)((b ^ (uint32_t)((i >> 1) << 5)) + (i & 1 ? kV : 0) + mb * 64 * D);
+      };
+      bf16x8_t f[kPre];
+#pragma unroll
+      for (int i = 0; i < kPre; ++i) f[i] = frag(i);
+      __builtin_amdgcn_sched_barrier(0);
+      tile::static_for<NA>([&](auto ic) __attribute__((always_inline)) {
+        constexpr int i = decltype(ic)::value, kk = i >> 1;
+        if constexpr (i & 1)
+          dP[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % kPre], bdo[kk], kk ? dP[mb] : f32x16_t{}, 0, 0, 0);
+        else
+          S[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % kPre], bq[kk], kk ? S[mb] : f32x16_t{}, 0, 0, 0);
+        if constexpr (i + kPre < NA) f[i % kPre] = frag(i + kPre);
+        hook(ic);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    };
+    auto dq_half = [&](auto mbc, auto&& hook) __attribute__((always_inline)) {
+      constexpr int mb = decltype(mbc)::value;
+      const uint32_t b = base(st, a_tr);
+      bf16x8_t f[kPre];
+#pragma unroll
+      for (int i = 0; i < kPre; ++i) f[i] = ktf(b, mb, i / NDB, i % NDB);
+      __builtin_amdgcn_sched_barrier(0);
+      tile::static_for<NQ>([&](auto ic) __attribute__((always_inline)) {
+        constexpr int i = decltype(ic)::value, j = i / NDB, db = i % NDB;
+        acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % kPre], ds[mb][j], acc[db], 0, 0, 0);
+        if constexpr (i + kPre < NQ) f[i % kPre] = ktf(b, mb, (i + kPre) / NDB, (i + kPre) % NDB);
+        hook(ic);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    };
+    auto mask = [&](auto mbc) __attribute__((always_inline)) {
+      constexpr int mb = decltype(mbc)::value;
+      if (partial) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) S[mb][i] = mb * 32 + (i >> 2) * 8 + (i & 3) < rel ? S[mb][i] : -INFINITY;
+      }
+    };
+    // dS of half mb in the slots after products 2 .. N-1 of another group
+    // (its last score product has landed by then)
+    auto finish = [&](auto mbc, auto nc, auto ic) __attribute__((always_inline)) {
+      constexpr int mb = decltype(mbc)::value, n = decltype(nc)::value - 2, k = decltype(ic)::value - 2;
+      if constexpr (k == 0) mask(mbc);
+      if constexpr (k >= 0)
+        tile::static_for<16 * (k + 1) / n - 16 * k / n>([&](auto uc) __attribute__((always_inline)) {
+          constexpr int i = 16 * k / n + decltype(uc)::value;
+          const float pr = fast_exp2(fmaf(S[mb][i], sl2, -lse2));
+          x[i % 8] = pr * (dP[mb][i] - dcol);
+          if constexpr (i % 8 == 7) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) ds[mb][i / 8][e] = (__bf16)x[e];
+          }
+        });
+    };
+    using H0 = std::integral_constant<int, 0>;
+    using H1 = std::integral_constant<int, 1>;
+    scores(H0{}, [&](auto) {});
+    scores(H1{}, [&](auto ic) __attribute__((always_inline)) { finish(H0{}, std::integral_constant<int, NA>{}, ic); });
+    dq_half(H0{}, [&](auto ic) __attribute__((always_inline)) { finish(H1{}, std::integral_constant<int, NQ>{}, ic); });
+    dq_half(H1{}, [&](auto) {});
+  };
 
-  Cursor C{0, 0, p.ranges[w.rng_begin], 1, 0};
-  Cursor L = C;
-  load(L);
+  // Step t computes stage t % 3; the loads of tile t+2 go to the stage of tile
+  // t-1, which every wavefront has read before this step's barrier, and each
+  // wavefront waits for its own loads of tile t before it (only those of tile
+  // t+1 may still be in flight).  Past the item's last tile the cursor stays
+  // on a valid one.
+  Cursor C{0, 0, load_scalar(&p.ranges[w.rng_begin])}, L = C;
+  load(L, 0);
+  advance(L);
+  load(L, 1);
   advance(L);
   int lim = lim_of(C.R);
-  for (;;) {
-    store();
-    __syncthreads();
-    if (L.ok) load(L);  // next tile, in flight during this one
-    const int kb = C.kt * KT;
-    const bool partial = kb + KT > C.R.min_lim;
-    const int rel = lim - kb - hf * 4;
-#pragma unroll
-    for (int mb = 0; mb < 2; ++mb) {
-      f32x16_t S, dP;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        S[i] = 0.f;
-        dP[i] = 0.f;
-      }
-#pragma unroll
-      for (int kk = 0; kk < NKK; ++kk) {
-        const int off = at(mb * 32 + l32, 2 * kk + hf);
-        S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8_t*>(&Ks[off]), bq[kk], S, 0, 0, 0);
-        dP = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8_t*>(&Vs[off]), bdo[kk], dP, 0, 0, 0);
-      }
-      // element i: key mb*32 + (i/4)*8 + hf*4 + i%4 of the tile, this lane's column
-      bf16x8_t ds[2];
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const bool vis = !partial || mb * 32 + (i >> 2) * 8 + (i & 3) < rel;
-        const float pr = vis ? fast_exp2(fmaf(S[i], sl2, -lse2)) : 0.f;
-        ds[i >> 3][i & 7] = (__bf16)(pr * (dP[i] - dcol));
-      }
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int db = 0; db < NDB; ++db) {
-          acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ktf(mb, j, db), ds[j], acc[db], 0, 0, 0);
-        }
-    }
-    __syncthreads();
-    const int ri_before = C.ri;
-    advance(C);
-    if (!C.ok) break;
-    if (C.ri != ri_before) lim = lim_of(C.R);
+  int s = 0;
+  for (int t = 0; t < n_tiles; ++t) {
+    tile::wait_vm<2 * IPW>();
+    tile::bar();
+    load(L, s == 0 ? 2 : s - 1);
     advance(L);
+    const int kb = C.kt * KT;
+    tile_step(lds0 + s * (4 * kTile), kb + KT > C.R.min_lim, lim - kb - hf * 4);
+    const int ri = C.ri;
+    advance(C);
+    if (C.ri != ri && t + 1 < n_tiles) lim = lim_of(C.R);
+    s = s == 2 ? 0 : s + 1;
   }
+  __builtin_amdgcn_s_waitcnt(0);
 
   if (!valid) return;
   const float sc = p.scale;
-  uint16_t* op = static_cast<uint16_t*>(p.dq) + qoff;
+  uint16_t* op = static_cast<uint16_t*>(p.dq) + row * D;
 #pragma unroll
   for (int db = 0; db < NDB; ++db)
 #pragma unroll
     for (int i4 = 0; i4 < 4; ++i4) {
-      const int d0 = db * 32 + i4 * 8 + hf * 4;
+      const f32x16_t& v = acc[db];
       uint2 pk;
-      pk.x = (uint32_t)f32_to_bf16_bits(acc[db][4 * i4] * sc) | ((uint32_t)f32_to_bf16_bits(acc[db][4 * i4 + 1] * sc) << 16);
-      pk.y = (uint32_t)f32_to_bf16_bits(acc[db][4 * i4 + 2] * sc) |
-             ((uint32_t)f32_to_bf16_bits(acc[db][4 * i4 + 3] * sc) << 16);
-      *reinterpret_cast<uint2*>(op + d0) = pk;
+      pk.x = (uint32_t)f32_to_bf16_bits(v[4 * i4] * sc) | ((uint32_t)f32_to_bf16_bits(v[4 * i4 + 1] * sc) << 16);
+      pk.y = (uint32_t)f32_to_bf16_bits(v[4 * i4 + 2] * sc) | ((uint32_t)f32_to_bf16_bits(v[4 * i4 + 3] * sc) << 16);
+      *reinterpret_cast<uint2*>(op + db * 32 + i4 * 8 + hf * 4) = pk;
     }
 }
 
@@ -698,14 +747,14 @@ void launch_dkdv(const BwdParams& p, int n_bwd, hipStream_t stream) {
 }  // namespace
 
 hipError_t launch_tree_attn_bwd(const BwdParams& p, int n_work, int n_bwd, int D, hipStream_t stream) {
-  const dim3 blk256(256), blk512(kThreads);
+  const dim3 blk256(256);
   if (p.n_btokens > 0)
     hipLaunchKernelGGL(bwd_tokens_kernel, dim3((unsigned)((p.n_btokens + 3) / 4)), blk256, 0, stream, p);
   if (n_work > 0) {
     if (D == 64)
-      hipLaunchKernelGGL((bwd_dq_kernel<64>), dim3(n_work), blk512, 0, stream, p);
+      hipLaunchKernelGGL((bwd_dq_kernel<64>), dim3(n_work), dim3(kThreads), 0, stream, p);
     else
-      hipLaunchKernelGGL((bwd_dq_kernel<128>), dim3(n_work), blk512, 0, stream, p);
+      hipLaunchKernelGGL((bwd_dq_kernel<128>), dim3(n_work), dim3(kThreads), 0, stream, p);
   }
   if (n_bwd > 0) {
     if (D == 64)
