@@ -329,7 +329,13 @@ __device__ __forceinline__ void fwd_item(const TileParams& p, int item) {
       const int e = 3 * j;
       return max3f(Sb[Y][e >> 4][e & 15], Sb[Y][(e + 1) >> 4][(e + 1) & 15], Sb[Y][(e + 2) >> 4][(e + 2) & 15]);
     };
-    if constexpr (k == 0) { t1[0] = e3(0); t1[1] = e3(1); t1[2] = e3(2); }
+    if constexpr (k == 0) {
+      // max3f is an instruction of its own, so the compiler does not see that
+      // it reads products that may still be on their way (an unmasked tile has
+      // nothing between); 12 wait states is what it leaves elsewhere.
+      asm volatile("s_nop 7\n\ts_nop 3" : "+v"(Sb[Y][0]), "+v"(Sb[Y][1]));
+      t1[0] = e3(0); t1[1] = e3(1); t1[2] = e3(2);
+    }
     if constexpr (k == 1) { t1[3] = e3(3); t1[4] = e3(4); }
     if constexpr (k == 2) { t1[5] = e3(5); t1[6] = e3(6); t1[7] = e3(7); }
     if constexpr (k == 3) { t1[8] = e3(8); t1[9] = e3(9); t1[10] = max3f(Sb[Y][1][14], Sb[Y][1][15], Sb[Y][1][15]); }
