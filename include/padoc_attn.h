@@ -143,7 +143,8 @@ typedef struct {
                                     wavefronts each) within 3/16 of this,
                                     private keys into about 2x this many
                                     wavefront items (chunks of 512 to 8192
-                                    keys)                                    */
+                                    keys; of 256 where 512 would give fewer
+                                    items than this)                         */
 } padoc_tree_desc;
 
 typedef struct padoc_plan padoc_plan;

@@ -671,7 +671,8 @@ void build_decode(padoc_plan& P, Builder& B, const AncList& anc, const padoc_tre
   pvis.clear();
   svis_at.assign(1, 0);
   pvis_at.assign(1, 0);
-  int64_t total_p = 0;
+  int64_t total_p = 0, items_p = 0;  // private keys, and items in chunks of kLongChunk
+  constexpr int64_t kLongChunk = 512, kShortChunk = 256;
   for (const Task& t : stasks) {
     B.visible(t, shared, svis);
     svis_at.push_back(svis.size());
@@ -679,16 +680,26 @@ void build_decode(padoc_plan& P, Builder& B, const AncList& anc, const padoc_tre
   for (const Task& t : ptasks) {
     B.visible_own(t, pvis);
     const int64_t splits = ceil_div((int64_t)t.count * G, kPrivateCols);
-    for (size_t r = pvis_at.back(); r < pvis.size(); ++r) total_p += round_up(pvis[r].n_keys, 32) * P.Hkv * splits;
+    for (size_t r = pvis_at.back(); r < pvis.size(); ++r) {
+      total_p += round_up(pvis[r].n_keys, 32) * P.Hkv * splits;
+      items_p += ceil_div(pvis[r].n_keys, kLongChunk) * P.Hkv * splits;
+    }
     pvis_at.push_back(pvis.size());
   }
   const int64_t tw = d->target_workgroups > 0 ? d->target_workgroups : 1024;
-  auto chunk_keys = [&](int64_t total, int64_t pieces) {
+  auto chunk_keys = [&](int64_t total, int64_t pieces, int64_t least) {
     if (d->max_chunk_keys > 0) return (int64_t)d->max_chunk_keys;
     const int64_t ch = round_up(std::max<int64_t>(1, ceil_div(total, pieces)), 64);
-    return std::min<int64_t>(std::max<int64_t>(ch, 512), padoc::kMaxItemKeys);
+    return std::min<int64_t>(std::max<int64_t>(ch, least), padoc::kMaxItemKeys);
   };
-  const int64_t CHp = chunk_keys(total_p, 2 * tw);
+  // A chunk is one wavefront's serial stream, so where chunks of 512 would
+  // make fewer items than half of the wavefronts, they are 256 (8 pages of 2,048
+  // prefix keys and 32 branches of up to 600: 584 -> 914 items, 59.0 -> 47.1
+  // us; 2 pages with 64 branches of up to 1,500: 536 -> 944 items, 61.2 ->
+  // 52.4); 192 and fewer were no faster there (50.0, 48.5), and with more items
+  // shorter chunks cost more partials than they save (1,552 items of the dense
+  // mixed step: 87.3 us, 93.0 with 256).
+  const int64_t CHp = chunk_keys(total_p, 2 * tw, items_p < tw ? kShortChunk : kLongChunk);
   // Shared keys: every tile item takes a whole compute unit (its registers)
   // for its duration, and the private items stream keys on the units the
   // tile items leave free.  The tile items are capped at three quarters of
