@@ -469,6 +469,7 @@ class DecodeSession:
         h = C.c_void_p()
         _lib.check(_lib.lib().padoc_session_create(C.byref(desc), C.byref(h)))
         self._h = h
+        self._streams = _lib.streams(h)
         self.n_open = 0
         self.n_kv_rows = self.n_q_rows = 0
         self.workspace_bytes = 0
@@ -492,13 +493,20 @@ class DecodeSession:
             pass
 
     def open(self, parent: int = -1, fork: int = 0) -> int:
-        i = C.c_int32(0)
-        _lib.check(_lib.lib().padoc_session_open(self.handle, int(parent), int(fork), C.byref(i)))
+        if self._h is None:
+            raise ValueError("session is closed")
+        i = self._streams.open(parent, fork)
+        if i < 0:
+            _lib.check(i)
         self.n_open += 1
-        return int(i.value)
+        return i
 
     def close(self, stream_id: int) -> None:
-        _lib.check(_lib.lib().padoc_session_close(self.handle, int(stream_id)))
+        if self._h is None:
+            raise ValueError("session is closed")
+        st = self._streams.close(stream_id)
+        if st:
+            _lib.check(st)
         self.n_open -= 1
 
     def select(self, max_rows: int, priority=None):

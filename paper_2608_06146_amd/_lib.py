@@ -155,6 +155,14 @@ class PadocError(RuntimeError):
         self.status = status
 
 
+def streams(handle):
+    """The native ``open`` / ``close`` of session ``handle``'s streams."""
+    from ._streams import Streams
+    L = lib()
+    return Streams(handle.value, C.cast(L.padoc_session_open, C.c_void_p).value,
+                   C.cast(L.padoc_session_close, C.c_void_p).value)
+
+
 def check(status: int) -> None:
     if status != OK:
         raise PadocError(status, lib().padoc_last_error().decode(errors="replace"))

@@ -1,4 +1,5 @@
-"""Build ``libpadoc_attn.so`` in-tree with hipcc for gfx950.
+"""Build ``libpadoc_attn.so`` in-tree with hipcc for gfx950, and the small
+CPython module ``_streams`` beside it.
 
     python -m paper_2608_06146_amd.build            # incremental
     python -m paper_2608_06146_amd.build --force    # rebuild everything
@@ -15,11 +16,13 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libpadoc_attn.so")
+STREAMS = os.path.join(PKG, "_streams" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 ARCH = os.environ.get("PADOC_OFFLOAD_ARCH", "gfx950")
 
 SOURCES = [
@@ -91,6 +94,13 @@ def build(force: bool = True, verbose: bool = False) -> str:
     if r.returncode != 0:
         raise RuntimeError(f"link failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
     os.replace(tmp, LIB)
+    tmp = STREAMS + ".tmp"
+    cmd = [cc, "-O2", "-std=c++17", "-fPIC", "-Wall", "-shared", "-no-hip-rt", "-I", sysconfig.get_paths()["include"], "-o", tmp,
+           os.path.join(PKG, "csrc/python/streams.cpp")]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"link failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
+    os.replace(tmp, STREAMS)
     if verbose:
         print(f"built {LIB}")
     return LIB

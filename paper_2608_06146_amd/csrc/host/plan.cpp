@@ -101,6 +101,13 @@ void sort_by_cost(std::vector<padoc::WorkRec>& w, std::vector<padoc::WorkRec>& t
   for (const auto& x : tmp) w[start[mx - x.cost]++] = x;
 }
 
+// A partial of a decode step: the (query row, KV head) it belongs to and the
+// slot it is written to.
+struct Part {
+  uint32_t row;  // row * Hkv + kvh
+  int32_t slot;
+};
+
 // Working vectors of the planner, kept per thread so that repeated planning
 // (a new schedule every decode step) reuses their memory.
 struct Scratch {
@@ -113,7 +120,7 @@ struct Scratch {
   std::vector<VisRange> vis, svis, pvis;
   std::vector<size_t> svis_at, pvis_at;
   std::vector<Piece> pieces;
-  std::vector<std::pair<size_t, int32_t>> parts;
+  std::vector<Part> parts;
   std::vector<padoc::WorkRec> sitems, pitems, tmp;
   std::vector<std::tuple<int32_t, int64_t, int32_t, uint32_t>> xkeys;
   std::vector<uint32_t> xgroup, xorder;
@@ -747,11 +754,15 @@ void build_decode(padoc_plan& P, Builder& B, const AncList& anc, const padoc_tre
     CHs = 64 * lo;
   }
 
-  // (row * Hkv + kvh, slot) of every partial, in creation order.
+  // Every partial in creation order, counted per row as it is listed (a step
+  // of 512 rows over 8 pages lists 6,144; n_parts of the vector's elements
+  // are in use, so that the list grows without a check per partial).
   auto& parts = S.parts;
+  size_t n_parts = 0;
+  const size_t n_rows = (size_t)P.num_q_rows * P.Hkv;
+  P.comb_ptr.assign(n_rows + 1, 0);
   auto& sitems = S.sitems;
   auto& pitems = S.pitems;
-  parts.clear();
   sitems.clear();
   pitems.clear();
   auto emit = [&](const Task& task, int32_t tok_begin, const std::vector<VisRange>& vis, const Piece* pieces,
@@ -762,8 +773,14 @@ void build_decode(padoc_plan& P, Builder& B, const AncList& anc, const padoc_tre
     if (rc == 0) return;
     for (int32_t kvh = 0; kvh < P.Hkv; ++kvh) {
       const int32_t base = (int32_t)P.n_slots;
-      for (int32_t i = 0; i < ntok; ++i)
-        if (B.sees[i]) parts.push_back({(size_t)P.toks[tok_begin + i] * P.Hkv + kvh, base + i * G});
+      if (parts.size() < n_parts + ntok) parts.resize(2 * (n_parts + ntok));
+      const int32_t* tok = P.toks.data() + tok_begin;
+      for (int32_t i = 0; i < ntok; ++i) {
+        if (!B.sees[i]) continue;
+        const size_t row = (size_t)tok[i] * P.Hkv + kvh;
+        parts[n_parts++] = {(uint32_t)row, base + i * G};
+        ++P.comb_ptr[row + 1];
+      }
       P.n_slots += (int64_t)ntok * G;
       for (int32_t c0 = 0; c0 < ntok * G; c0 += width) {
         padoc::WorkRec w{};
@@ -840,7 +857,10 @@ void build_decode(padoc_plan& P, Builder& B, const AncList& anc, const padoc_tre
       const int32_t cost = 1 + (int32_t)ceil_div(take, P.tile_keys);
       for (int32_t kvh = 0; kvh < P.Hkv; ++kvh) {
         const int32_t base = (int32_t)P.n_slots;
-        parts.push_back({(size_t)P.toks[tb] * P.Hkv + kvh, base});
+        if (parts.size() == n_parts) parts.resize(2 * n_parts + 64);
+        const size_t row = (size_t)P.toks[tb] * P.Hkv + kvh;
+        parts[n_parts++] = {(uint32_t)row, base};
+        ++P.comb_ptr[row + 1];
         P.n_slots += G;
         for (int32_t c0 = 0; c0 < G; c0 += kPrivateCols) {
           padoc::WorkRec w{};
@@ -885,15 +905,12 @@ void build_decode(padoc_plan& P, Builder& B, const AncList& anc, const padoc_tre
 
   // Combine map: slots per (row, KV head) in creation order (stable counting
   // sort of the partials by row).
-  const size_t n_rows = (size_t)P.num_q_rows * P.Hkv;
-  P.comb_ptr.assign(n_rows + 1, 0);
-  for (const auto& pr : parts) ++P.comb_ptr[pr.first + 1];
   for (size_t r = 0; r < n_rows; ++r) P.comb_ptr[r + 1] += P.comb_ptr[r];
-  P.comb_slot.resize(parts.size());
+  P.comb_slot.resize(n_parts);
   {
     auto& fill = S.fill;
     fill.assign(P.comb_ptr.begin(), P.comb_ptr.end() - 1);
-    for (const auto& pr : parts) P.comb_slot[fill[pr.first]++] = pr.second;
+    for (size_t i = 0; i < n_parts; ++i) P.comb_slot[fill[parts[i].row]++] = parts[i].slot;
   }
   for (size_t r = 0; r < n_rows; ++r)
     if (P.comb_ptr[r + 1] > P.comb_ptr[r]) P.comb_rows.push_back((int32_t)r);
