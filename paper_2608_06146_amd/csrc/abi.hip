@@ -154,6 +154,7 @@ padoc_status run(const padoc_plan* P, const void* q, const void* k, const void* 
   tp.block_table = bt;
   tp.work = at<WorkRec>(ws, P->off_work);
   tp.ranges = at<RangeRec>(ws, P->off_ranges);
+  tp.first = at<RangeRec>(ws, P->off_first);
   tp.lims = at<int32_t>(ws, P->off_lims);
   tp.toks = at<int32_t>(ws, P->off_toks);
   tp.part_o = reinterpret_cast<float*>(static_cast<char*>(ws) + P->off_part_o);

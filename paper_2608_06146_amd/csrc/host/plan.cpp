@@ -950,7 +950,11 @@ void serialise_backward(padoc_plan& P) {
 void serialise(padoc_plan& P) {
   P.off_work = 0;
   P.off_ranges = align256(P.off_work + P.work.size() * sizeof(padoc::WorkRec));
-  P.off_lims = align256(P.off_ranges + P.ranges.size() * sizeof(padoc::RangeRec));
+  // decode, bf16: each tile item's first range once more, at the item's index,
+  // with the item's number of tiles in its reserved field
+  const size_t n_first = P.kind == 1 && P.dtype == PADOC_BF16 ? (size_t)P.n_work_shared : 0;
+  P.off_first = align256(P.off_ranges + P.ranges.size() * sizeof(padoc::RangeRec));
+  P.off_lims = align256(P.off_first + n_first * sizeof(padoc::RangeRec));
   P.off_toks = align256(P.off_lims + P.lims.size() * 4);
   P.off_comb_slot = align256(P.off_toks + P.toks.size() * 4);
   P.off_comb_rows = align256(P.off_comb_slot + P.comb_slot.size() * 4);
@@ -969,7 +973,16 @@ void serialise(padoc_plan& P) {
     std::memset(b + off + bytes, 0, end - off - bytes);
   };
   section(P.off_work, P.work.data(), P.work.size() * sizeof(padoc::WorkRec), P.off_ranges);
-  section(P.off_ranges, P.ranges.data(), P.ranges.size() * sizeof(padoc::RangeRec), P.off_lims);
+  section(P.off_ranges, P.ranges.data(), P.ranges.size() * sizeof(padoc::RangeRec), P.off_first);
+  padoc::RangeRec* first = reinterpret_cast<padoc::RangeRec*>(b + P.off_first);
+  for (size_t i = 0; i < n_first; ++i) {
+    const padoc::WorkRec& w = P.work[i];
+    first[i] = P.ranges[w.rng_begin];
+    first[i].reserved = 0;
+    for (int32_t r = 0; r < w.rng_count; ++r)
+      first[i].reserved += (int32_t)ceil_div(P.ranges[w.rng_begin + r].n_keys, kTileKeys);
+  }
+  std::memset(first + n_first, 0, P.off_lims - P.off_first - n_first * sizeof(padoc::RangeRec));
   section(P.off_lims, P.lims.data(), P.lims.size() * 4, P.off_toks);
   section(P.off_toks, P.toks.data(), P.toks.size() * 4, P.off_comb_slot);
   section(P.off_comb_slot, P.comb_slot.data(), P.comb_slot.size() * 4, P.off_comb_rows);

@@ -40,7 +40,8 @@
 // Reference maximum.  A column's probabilities are 2^(s*scale*log2(e) - m)
 // for a reference m that is raised only when a tile's maximum exceeds it by
 // more than 2^8, so every probability stays <= 2^8; the exact row maximum is
-// computed only for the first tile and when a tile's probabilities sum to
+// computed only for the first tile, for the first tile in which some column
+// sees a key, and when a tile's probabilities sum to
 // more than 2^8 (or overflow) -- then the tile's scores are recomputed from
 // K, still in its stage, and the accumulator is rescaled.  That is exactly
 // the set of tiles whose maximum passes the reference by more than the
@@ -58,6 +59,16 @@
 // tile into a stage nobody reads), so the counts are exact, and the item
 // waits for all of them before it ends.  Keys past a range's end read the
 // range's last row (the buffer may end there); their scores are masked.
+//
+// Start and end of an item.  A workgroup fills a compute unit, so nothing
+// overlaps them: a decode step of one page (36 items of two tiles) is 8.7 us
+// of chain, of which 2.0 until the first K/V loads are issued, 1.0 for the
+// first scores, 3.5 for the two steps and, before the results went through
+// LDS, 1.5 for the stores.  The first scores wait for two tiles, the third
+// lands during them; a paged item starts from one record read with the work
+// record.  Whole steps, before / after (with the exact path left to tiles in
+// which a column has something to see): one page 22.7 / 20.5 us; forward of
+// one page 66.4 / 65.0, of eight 851 / 842, 64-wide heads 569 / 565.
 #pragma once
 
 #include "tile_common.hpp"
@@ -151,16 +162,47 @@ __device__ __forceinline__ void fwd_item(const TileParams& p, int item) {
   const int G = p.G;
   const int kvh = w.kvh;
 
+  // Paged items (decode: short ones, each latency of whose start counts) have
+  // a copy of their first range at the item's index, read together with the
+  // work record, that also holds the number of tiles.
+  const RangeRec R0 = PAGED ? load_scalar(&p.first[item]) : load_scalar(&p.ranges[w.rng_begin]);
   int n_tiles = 0;
-  for (int r = 0; r < w.rng_count; ++r)
-    n_tiles += (load_scalar(&p.ranges[w.rng_begin + r]).n_keys + KT - 1) / KT;
-  n_tiles = __builtin_amdgcn_readfirstlane(n_tiles);
+  if constexpr (PAGED) {
+    n_tiles = R0.reserved;
+  } else {
+    for (int r = 0; r < w.rng_count; ++r)
+      n_tiles += (load_scalar(&p.ranges[w.rng_begin + r]).n_keys + KT - 1) / KT;
+    n_tiles = __builtin_amdgcn_readfirstlane(n_tiles);
+  }
 
   const int col = wave * 32 + l32;
   const int tok = col / G;
   const bool valid = tok < w.ntok;
   const int32_t qrow = valid ? p.toks[w.tok_begin + tok] : 0;
   const int32_t hq = kvh * G + (col - tok * G);
+
+  // Block ids of every tile of a paged item (thread u: tile u / NBT, block
+  // u % NBT; an item has at most kMaxItemTiles tiles), read once into LDS so
+  // no step waits for a block-table read, and before Q, whose rows need one
+  // more read (the token's) than the ids do.  Blocks wholly past a range's
+  // end take the id of the tile's first block.
+  if constexpr (PAGED) {
+    const int tile = tid / NBT, bi = tid % NBT;
+    if (tile < n_tiles) {
+      int64_t start = R0.kv_start;
+      int kbase = tile * KT, nk = R0.n_keys;
+      for (int r = 1, tb = (R0.n_keys + KT - 1) / KT; r < w.rng_count; ++r) {
+        const RangeRec R = load_scalar(&p.ranges[w.rng_begin + r]);
+        if (tile >= tb) {
+          start = R.kv_start;
+          kbase = (tile - tb) * KT;
+          nk = R.n_keys;
+        }
+        tb += (R.n_keys + KT - 1) / KT;
+      }
+      tile_ids[tid] = p.block_table[start + (kbase >> 4) + ((kbase + bi * kBlock < nk) ? bi : 0)];
+    }
+  }
 
   bf16x8_t bq[NKK];
   {
@@ -282,15 +324,15 @@ __device__ __forceinline__ void fwd_item(const TileParams& p, int item) {
     dma4(lb, lim_off < 0 || !valid ? 0u : 4u * tok, lds_addr(dst + wave * 64));
   };
 
-  const RangeRec R0 = load_scalar(&p.ranges[w.rng_begin]);
   Cursor Lk{0, 0, R0, 1, 0};  // next tile to load (K, V, limits)
   Cursor C = Lk;              // tile whose scores were computed last
 
   float m_run = -INFINITY, l_run = 0.f, m_sub = 0.f, alpha = 1.f;
   bool any_raise = false;
-  // Some valid column has seen no key yet (its reference is still -inf and
-  // its probabilities are taken relative to 0): the exact path runs.
-  bool any_fresh = true;
+  // The column has seen no key yet: its reference is still -inf and its
+  // probabilities are taken relative to 0, so the first tile in which it sees
+  // one (`sees`, of the tile masked last) takes the exact path.
+  bool fresh = false, sees = true;
   f32x16_t acc[NDB];
 #pragma unroll
   for (int db = 0; db < NDB; ++db)
@@ -304,11 +346,14 @@ __device__ __forceinline__ void fwd_item(const TileParams& p, int item) {
   auto mask_tile = [&](auto yc, const int32_t* lim) {
     constexpr int Y = decltype(yc)::value;
     const int kb = C.kt * KT;
+    sees = true;
     if (kb + KT > C.R.min_lim) {
       // element i of half mb of lane (col, hf) is tile row mb*32 + 8*(i/4) +
       // 4*hf + i%4; paged rows are in slot order (bits 2 and 3 of the key
       // swapped within each block)
-      const int rel = (C.R.lim_off < 0 ? C.R.n_keys : (valid ? lim[tid] : 0)) - kb - hf * (PAGED ? 8 : 4);
+      const int left = (C.R.lim_off < 0 ? C.R.n_keys : (valid ? lim[tid] : 0)) - kb;
+      const int rel = left - hf * (PAGED ? 8 : 4);
+      sees = left > 0;
 #pragma unroll
       for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
@@ -353,7 +398,7 @@ __device__ __forceinline__ void fwd_item(const TileParams& p, int item) {
       m_run = raise ? mx : m_run;
       m_sub = m_run == -INFINITY ? 0.f : m_run;
       any_raise = __any(raise);
-      any_fresh = __any(valid && m_run == -INFINITY);
+      fresh = valid && m_run == -INFINITY;
     }
   };
   // Exponentials of score buffer Y, in pieces 0..15 (two scores each; every
@@ -485,42 +530,25 @@ __device__ __forceinline__ void fwd_item(const TileParams& p, int item) {
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
   using I2 = std::integral_constant<int, 2>;
-  if constexpr (PAGED) {
-    // The block ids of every tile of the item (thread u: tile u / NBT, block
-    // u % NBT; an item has at most kMaxItemTiles tiles), read once into LDS
-    // so no step waits for a block-table read.  Blocks wholly past a range's
-    // end take the id of the tile's first block.
-    const int tile = tid / NBT, bi = tid % NBT;
-    if (tile < n_tiles) {
-      int64_t start = 0;
-      int kbase = 0, nk = 0;
-      for (int r = 0, tb = 0; r < w.rng_count; ++r) {
-        const RangeRec R = load_scalar(&p.ranges[w.rng_begin + r]);
-        const int nt = (R.n_keys + KT - 1) / KT;
-        if (tile >= tb && tile < tb + nt) {
-          start = R.kv_start;
-          kbase = (tile - tb) * KT;
-          nk = R.n_keys;
-        }
-        tb += nt;
-      }
-      tile_ids[tid] = p.block_table[start + (kbase >> 4) + ((kbase + bi * kBlock < nk) ? bi : 0)];
-    }
-    __builtin_amdgcn_s_waitcnt(0);
-    bar();
-  }
-  static_for<3>([&](auto sc) {
+  auto load_next = [&](auto sc) {
     const int ids = tile_blocks(Lk);
     load_tile(Kg, Lk, kst(sc), ld_k, false, ids);
     load_tile(Vg, Lk, vst(sc), ld_v, true, ids);
     load_lim(Lk, lst(sc));
     advance(Lk);
-  });
+  };
+  if constexpr (PAGED) {
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // the ids are in LDS; Q may be on its way
+    bar();
+  }
+  load_next(I0{});
+  load_next(I1{});
   __builtin_amdgcn_s_waitcnt(0);
   bar();
+  load_next(I2{});
   if constexpr (PAGED) {
     zero_v_tail(vst(I0{}));
-    __builtin_amdgcn_s_waitcnt(0);
+    __builtin_amdgcn_s_waitcnt(0xC07F);
     bar();
   }
   s_product(I0{}, I0{}, [&](auto) {});
@@ -557,7 +585,7 @@ __device__ __forceinline__ void fwd_item(const TileParams& p, int item) {
     // Tile t's probabilities and sums are complete here (else the compiler
     // sinks their computation past the branches below, next to their use).
     asm volatile("" ::"v"(P[0][0]), "v"(P[0][1]), "v"(P[1][0]), "v"(P[1][1]), "v"(ls0), "v"(ls1));
-    if (any_fresh || __any(!(ls0 + ls1 <= 256.f))) {
+    if (__any(!(ls0 + ls1 <= 256.f) || (fresh && sees))) {
       // some probability exceeds 2^8 (or overflowed): the tile's maximum
       // passed the reference by more than the slack (or a column has no
       // reference yet)
@@ -605,42 +633,63 @@ __device__ __forceinline__ void fwd_item(const TileParams& p, int item) {
   }
   __builtin_amdgcn_s_waitcnt(0);
 
+  // The results leave through LDS, each wavefront through 32 rows of its own
+  // (a stage's bytes of fp32, or half of them of bf16), so that a store writes
+  // whole rows: from the product's layout it would write 32 pieces of 32 (16)
+  // bytes, a quarter (eighth) of a line each.  16-byte chunk c of row r sits
+  // at c ^ r (modulo the chunks of a row), which spreads both sides over the
+  // banks.
+  bar();  // every wavefront is done with the stages
   const float lt = l_run + __shfl_xor(l_run, 32);
-  if (!valid) return;
+  char* rows = reinterpret_cast<char*>(smem) + wave * (32 * D * 4);
+  const int n_rows = min(32, w.ntok * G - wave * 32);  // columns of this wavefront in use
   if constexpr (PAGED) {
     // split partial of column col: unnormalised O, reference maximum (log2
     // units), sum
-    const int64_t slot = (int64_t)w.out_base + col;
-    float* op = p.part_o + slot * D;
+    constexpr int NC = D / 4, RP = 64 / NC;  // chunks of a row, rows of a store
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+      for (int i4 = 0; i4 < 4; ++i4)
+        *reinterpret_cast<float4*>(rows + (l32 * NC + ((db * 8 + i4 * 2 + hf) ^ (l32 & (NC - 1)))) * 16) =
+            make_float4(acc[db][4 * i4], acc[db][4 * i4 + 1], acc[db][4 * i4 + 2], acc[db][4 * i4 + 3]);
+    asm volatile("" ::: "memory");
+    const int c = lane & (NC - 1);
+    float* op = p.part_o + ((int64_t)w.out_base + wave * 32) * D + c * 4;
+#pragma unroll
+    for (int k = 0; k < 32 / RP; ++k) {
+      const int r = k * RP + lane / NC;
+      const float4 x = *reinterpret_cast<const float4*>(rows + (r * NC + (c ^ (r & (NC - 1)))) * 16);
+      if (r < n_rows) *reinterpret_cast<float4*>(op + r * D) = x;
+    }
+    if (valid && hf == 0)
+      *reinterpret_cast<float2*>(p.part_ml + 2 * ((int64_t)w.out_base + col)) = make_float2(m_run, lt);
+  } else {
+    constexpr int NC = D / 8, RP = 64 / NC;
+    const float inv = 1.f / lt;
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
       for (int i4 = 0; i4 < 4; ++i4) {
-        const int d0 = db * 32 + i4 * 8 + hf * 4;
-        *reinterpret_cast<float4*>(op + d0) =
-            make_float4(acc[db][4 * i4], acc[db][4 * i4 + 1], acc[db][4 * i4 + 2], acc[db][4 * i4 + 3]);
+        uint2 pk;
+        pk.x = (uint32_t)f32_to_bf16_bits(acc[db][4 * i4] * inv) |
+               ((uint32_t)f32_to_bf16_bits(acc[db][4 * i4 + 1] * inv) << 16);
+        pk.y = (uint32_t)f32_to_bf16_bits(acc[db][4 * i4 + 2] * inv) |
+               ((uint32_t)f32_to_bf16_bits(acc[db][4 * i4 + 3] * inv) << 16);
+        *reinterpret_cast<uint2*>(rows + (l32 * NC + ((db * 4 + i4) ^ (l32 & (NC - 1)))) * 16 + 8 * hf) = pk;
       }
-    if (hf == 0) {
-      p.part_ml[2 * slot] = m_run;
-      p.part_ml[2 * slot + 1] = lt;
+    asm volatile("" ::: "memory");
+    const int c = lane & (NC - 1);
+#pragma unroll
+    for (int k = 0; k < 32 / RP; ++k) {
+      const int r = k * RP + lane / NC;
+      const uint4 x = *reinterpret_cast<const uint4*>(rows + (r * NC + (c ^ (r & (NC - 1)))) * 16);
+      const int64_t qr = __shfl(qrow, r);
+      const int hr = __shfl(hq, r);
+      if (r < n_rows) *reinterpret_cast<uint4*>(static_cast<uint16_t*>(p.o) + (qr * p.Hq + hr) * D + c * 8) = x;
     }
-    return;
+    if (valid && hf == 0) p.lse[(int64_t)qrow * p.Hq + hq] = (m_run + __log2f(lt)) * kLn2;
   }
-  const float inv = 1.f / lt;
-  uint16_t* op = static_cast<uint16_t*>(p.o) + ((int64_t)qrow * p.Hq + hq) * D;
-#pragma unroll
-  for (int db = 0; db < NDB; ++db)
-#pragma unroll
-    for (int i4 = 0; i4 < 4; ++i4) {
-      const int d0 = db * 32 + i4 * 8 + hf * 4;
-      uint2 pk;
-      pk.x = (uint32_t)f32_to_bf16_bits(acc[db][4 * i4] * inv) |
-             ((uint32_t)f32_to_bf16_bits(acc[db][4 * i4 + 1] * inv) << 16);
-      pk.y = (uint32_t)f32_to_bf16_bits(acc[db][4 * i4 + 2] * inv) |
-             ((uint32_t)f32_to_bf16_bits(acc[db][4 * i4 + 3] * inv) << 16);
-      *reinterpret_cast<uint2*>(op + d0) = pk;
-    }
-  if (hf == 0) p.lse[(int64_t)qrow * p.Hq + hq] = (m_run + __log2f(lt)) * kLn2;
 }
 
 }  // namespace tile

@@ -15,7 +15,8 @@
 // fetches partial j's slot, m and l (independent loads), the batch maximum
 // and weighted sum come from butterfly reductions over the group, and the
 // O rows are then summed in the planner's order with the weights passed by
-// shuffles, so their loads do not wait on each other.  Reductions and sums
+// shuffles; they are loaded U at a time, the first ones before the
+// reductions, which wait for m and l.  Reductions and sums
 // run in a fixed order: results are bitwise reproducible.
 #include "device_common.hpp"
 
@@ -70,6 +71,20 @@ __global__ __launch_bounds__(256) void lse_combine_kernel(CombineParams p) {
       m = v.x;
       l = v.y;
     }
+    // O rows of partials j0 .. j0+U-1 of the batch (one past the batch
+    // re-reads the last one and is skipped).
+    float x[U][PER];
+    auto load_o = [&](int j0) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int j = j0 + u < cnt ? j0 + u : cnt - 1;
+        const int32_t sj = __shfl(slot, j, LANES);
+        const vec_t* src = reinterpret_cast<const vec_t*>(p.part_o + (int64_t)sj * D + sub * PER);
+#pragma unroll
+        for (int k = 0; k < NV; ++k) *reinterpret_cast<vec_t*>(&x[u][VW * k]) = src[k];
+      }
+    };
+    load_o(0);
     float mb = m;
 #pragma unroll
     for (int s = 1; s < LANES; s <<= 1) mb = fmaxf(mb, __shfl_xor(mb, s, LANES));
@@ -85,18 +100,8 @@ __global__ __launch_bounds__(256) void lse_combine_kernel(CombineParams p) {
     M = Mn;
 #pragma unroll
     for (int k = 0; k < PER; ++k) o[k] *= alpha;
-    // U partials per round: all their loads are issued before the first
-    // product (a partial past the batch re-reads the last one and is skipped)
     for (int j0 = 0; j0 < cnt; j0 += U) {
-      float x[U][PER];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int j = j0 + u < cnt ? j0 + u : cnt - 1;
-        const int32_t sj = __shfl(slot, j, LANES);
-        const vec_t* src = reinterpret_cast<const vec_t*>(p.part_o + (int64_t)sj * D + sub * PER);
-#pragma unroll
-        for (int k = 0; k < NV; ++k) *reinterpret_cast<vec_t*>(&x[u][VW * k]) = src[k];
-      }
+      if (j0 > 0) load_o(j0);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         if (j0 + u < cnt) {

@@ -51,6 +51,7 @@ struct TileParams {
   const int32_t* block_table;  // paged mode
   const WorkRec* work;
   const RangeRec* ranges;
+  const RangeRec* first;      // decode, bf16: first range of tile item i, its tiles counted in `reserved`
   const int32_t* lims;
   const int32_t* toks;
   float* part_o;          // partial mode: [slots, D] unnormalised accumulators
