@@ -551,6 +551,28 @@ __device__ __forceinline__ void fwd_item(const TileParams& p, int item) {
     __builtin_amdgcn_s_waitcnt(0xC07F);
     bar();
   }
+  if (wave * 32 >= w.ntok * G) {
+    // No column of this wavefront is in use (an item of few tokens): it loads
+    // its pieces of the tiles, clears its part of V's tails and keeps the
+    // barriers, and leaves the SIMD's issue slots and matrix core to the
+    // wavefront that shares them (decode step of one page, half of each item
+    // unused: 20.73 -> 20.37 us; forward with 64-wide heads, seven to a KV
+    // head: 569 -> 563; all columns used: no difference).
+    for (int t = 0; t < n_tiles; ++t) {
+      wait_vm<2 * IPW + 1>();
+      bar();
+      advance(C);
+      if (t + 1 < n_tiles) zero_v_tail(smem + (4 + (t + 1) % 4) * SEL);
+      const int ids = tile_blocks(Lk);
+      load_tile(Kg, Lk, smem + ((t + 3) % 4) * SEL, ld_k, false, ids);
+      load_tile(Vg, Lk, smem + (4 + (t + 3) % 4) * SEL, ld_v, true, ids);
+      load_lim(Lk, Lb[(t + 3) % 4]);
+      advance(Lk);
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    bar();
+    return;
+  }
   s_product(I0{}, I0{}, [&](auto) {});
   mask_tile(I0{}, Lb[0]);
   static_for<7>([&](auto kc) { stats_piece(I0{}, kc); });
