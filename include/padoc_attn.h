@@ -144,7 +144,10 @@ typedef struct {
                                     private keys into about 2x this many
                                     wavefront items (chunks of 512 to 8192
                                     keys; of 256 where 512 would give fewer
-                                    items than this)                         */
+                                    items than this).  Packed bf16 plans: a
+                                    quarter of it is the number of compute
+                                    units that their longest items are cut
+                                    in two for                              */
 } padoc_tree_desc;
 
 typedef struct padoc_plan padoc_plan;

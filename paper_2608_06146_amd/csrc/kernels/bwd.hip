@@ -285,8 +285,21 @@ __global__ __launch_bounds__(kThreads) void bwd_dq_kernel(BwdParams p) {
   advance(L);
   load(L, 1);
   advance(L);
-  int lim = lim_of(C.R);
   int s = 0;
+  if (wave * 32 >= w.ntok * G) {
+    // No column of this wavefront is in use (half an item): its part of the
+    // loads and barriers, the SIMD left to the wavefront that shares it.
+    for (int t = 0; t < n_tiles; ++t) {
+      tile::wait_vm<2 * IPW>();
+      tile::bar();
+      load(L, s == 0 ? 2 : s - 1);
+      advance(L);
+      s = s == 2 ? 0 : s + 1;
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    return;
+  }
+  int lim = lim_of(C.R);
   for (int t = 0; t < n_tiles; ++t) {
     tile::wait_vm<2 * IPW>();
     tile::bar();

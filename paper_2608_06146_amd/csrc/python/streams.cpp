@@ -4,10 +4,10 @@
 // Such a call is tens of nanoseconds of work; through ctypes it costs 0.9 to
 // 1.4 us of argument objects, conversions and releases of the interpreter
 // lock, and a step of 64 branches makes 128 of them (a whole step with its
-// opens and closes, 512 rows over 8 pages: 148 us, 86 with these).  Here the arguments are
-// converted as ctypes converts them (int(), then the low 32 bits) and the lock
-// is kept.  The library is not linked: ctypes, which loads it on first use,
-// hands over the two addresses.
+// opens and closes, 512 rows over 8 pages: 148 us, 86 with these).  Here the
+// arguments are converted as ctypes converts them (int(), then the low 32
+// bits) and the lock is kept.  The library is not linked: ctypes, which loads
+// it on first use, hands over the two addresses.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
