@@ -104,6 +104,7 @@ def lib():
         raise RuntimeError(f"{LIB_PATH} is missing: build it with `python -m paper_2608_06146_amd.build` "
                            "(the HIP library is required; there is no fallback path)")
     L = C.CDLL(LIB_PATH)
+    from . import _streams  # noqa: F401  (built with it; not during the first session)
     vp, i32, i64, sz = C.c_void_p, C.c_int32, C.c_int64, C.c_size_t
     L.padoc_tree_from_pages.argtypes = [C.POINTER(Page), i32, i32, vp, i32, C.POINTER(i32)]
     L.padoc_tree_layout.argtypes = [vp, i32, i32]
@@ -157,8 +158,8 @@ class PadocError(RuntimeError):
 
 def streams(handle):
     """The native ``open`` / ``close`` of session ``handle``'s streams."""
-    from ._streams import Streams
     L = lib()
+    from ._streams import Streams  # loaded with the library
     return Streams(handle.value, C.cast(L.padoc_session_open, C.c_void_p).value,
                    C.cast(L.padoc_session_close, C.c_void_p).value)
 
