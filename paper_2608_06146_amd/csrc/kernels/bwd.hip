@@ -171,6 +171,10 @@ __global__ __launch_bounds__(kThreads) void bwd_dq_kernel(BwdParams p) {
   auto lim_of = [&](const RangeRec& R) -> int {
     return R.lim_off < 0 ? R.n_keys : (valid ? p.lims[R.lim_off + tok] : 0);
   };
+  // A limit is waited for before the step that uses it: pending at a loop's
+  // back edge, the compiler, which does not count the loads to LDS, could only
+  // wait for every load in flight in each step.
+  auto settle = [&](int& x) __attribute__((always_inline)) { asm volatile("" : "+v"(x)); };
 
   // Fragment addresses (bytes): rows of K or V: row mb*32 + l32, d = kk*16 +
   // hf*8 ..; K^T (d on M, keys on K) for keys mb*32 + 16j + 4*half + {0..3},
@@ -281,6 +285,7 @@ __global__ __launch_bounds__(kThreads) void bwd_dq_kernel(BwdParams p) {
   // t+1 may still be in flight).  Past the item's last tile the cursor stays
   // on a valid one.
   Cursor C{0, 0, load_scalar(&p.ranges[w.rng_begin])}, L = C;
+  int lim = lim_of(C.R);
   load(L, 0);
   advance(L);
   load(L, 1);
@@ -299,7 +304,7 @@ __global__ __launch_bounds__(kThreads) void bwd_dq_kernel(BwdParams p) {
     __builtin_amdgcn_s_waitcnt(0);
     return;
   }
-  int lim = lim_of(C.R);
+  settle(lim);
   for (int t = 0; t < n_tiles; ++t) {
     tile::wait_vm<2 * IPW>();
     tile::bar();
@@ -309,7 +314,10 @@ __global__ __launch_bounds__(kThreads) void bwd_dq_kernel(BwdParams p) {
     tile_step(lds0 + s * (4 * kTile), kb + KT > C.R.min_lim, lim - kb - hf * 4);
     const int ri = C.ri;
     advance(C);
-    if (C.ri != ri && t + 1 < n_tiles) lim = lim_of(C.R);
+    if (C.ri != ri && t + 1 < n_tiles) {
+      lim = lim_of(C.R);
+      settle(lim);
+    }
     s = s == 2 ? 0 : s + 1;
   }
   __builtin_amdgcn_s_waitcnt(0);

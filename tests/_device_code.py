@@ -136,3 +136,31 @@ def close_pairs(code, reader, writer, need):
                 continue
             todo += [(p, states + wait_states(w)) for p in preds[j]]
     return bad
+
+
+def blocks(code):
+    """Basic blocks as (first, last) index pairs with their successors."""
+    heads = {0} | {i.target for i in code if i.target is not None}
+    heads |= {n + 1 for n, i in enumerate(code) if i.op.startswith(("s_branch", "s_cbranch", "s_endpgm")) and n + 1 < len(code)}
+    heads = sorted(heads)
+    out = {}
+    for a, b in zip(heads, heads[1:] + [len(code)]):
+        last = code[b - 1]
+        nxt = [] if last.op.startswith(("s_branch", "s_endpgm")) or b == len(code) else [b]
+        out[a] = (b, nxt + ([last.target] if last.target is not None else []))
+    return out
+
+
+def loop_blocks(code):
+    """Instructions of every block that lies on a cycle."""
+    bl = blocks(code)
+    reach = {}
+    for a in bl:
+        seen, todo = set(), list(bl[a][1])
+        while todo:
+            x = todo.pop()
+            if x not in seen:
+                seen.add(x)
+                todo += bl[x][1]
+        reach[a] = seen
+    return [code[a:bl[a][0]] for a in bl if a in reach[a]]

@@ -86,3 +86,22 @@ def test_the_check_sees_a_missing_state(hazard, loop):
             for i, x in enumerate(lines + ["s_endpgm"]))
         pairs = dc.close_pairs(dc.parse(text)["k"], *HAZARDS[hazard])
         assert bool(pairs) == (states < need), (text, pairs)
+
+
+# Kernels whose loops keep loads to LDS in flight across steps, at counts they
+# wait for themselves.
+@pytest.mark.parametrize("kernel", ["tile_mfma_bf16", "bwd_dq"])
+def test_steps_do_not_drain_the_loads_in_flight(kernels, kernel):
+    """In a loop, only a block that itself loads into registers (the limits of
+    the next key range) waits for every load."""
+    found = 0
+    for name, code in kernels.items():
+        if kernel not in name:
+            continue
+        for block in dc.loop_blocks(code):
+            found += any("_lds_" in i.op for i in block)
+            if any(i.op == "s_waitcnt" and "vmcnt(0)" in " ".join(i.args) for i in block):
+                before = [i.op for i in code[:code.index(block[0])]][-8:]
+                assert any(op.startswith("global_load") and "_lds_" not in op for op in before + [i.op for i in block]), (
+                    name, block[0])
+    assert found >= 2
