@@ -439,7 +439,6 @@ __global__ __launch_bounds__(kThreads) void bwd_dkdv_kernel(BwdParams p) {
   const int t64 = COLS / G, h64 = COLS % G;
   int f_c = c_begin, f_t = c_begin / G, f_h = c_begin % G;  // next step to list
   int l_c = f_c, l_t = f_t, l_h = f_h;              // the step fetched last
-  int32_t f_row = 0;                                // query row of its column `lane` (wavefront 7)
   auto column = [&](int c, int t0, int h0, int& t, int& h) __attribute__((always_inline)) {
     const uint32_t x = (uint32_t)(h0 + lane);
     const uint32_t dt = (x * inv_g) >> 16;
@@ -447,10 +446,16 @@ __global__ __launch_bounds__(kThreads) void bwd_dkdv_kernel(BwdParams p) {
     t = ok ? t0 + (int)dt : t_end;
     h = ok ? (int)(x - dt * (uint32_t)G) : h_end;
   };
-  auto fetch_rows = [&]() __attribute__((always_inline)) {
+  // The query rows of the next columns into list u, by a load to LDS like the
+  // others: the compiler would wait for one into a register, and with it for
+  // every load in flight, in each step.
+  auto fetch_rows = [&](int u) __attribute__((always_inline)) {
     int t, h;
     column(f_c, f_t, f_h, t, h);
-    f_row = p.btoks[b.tok_begin + t];
+    if constexpr (WIDE)
+      tile::dma4_v(p.btoks + b.tok_begin + t, tile::lds_addr(cols[u].row));
+    else
+      tile::dma4(p.btoks, 4 * (uint32_t)(b.tok_begin + t), tile::lds_addr(cols[u].row));
     l_c = f_c, l_t = f_t, l_h = f_h;
     f_c += COLS;
     f_t += t64;
@@ -460,10 +465,10 @@ __global__ __launch_bounds__(kThreads) void bwd_dkdv_kernel(BwdParams p) {
       ++f_t;
     }
   };
-  auto list_rows = [&](int u) __attribute__((always_inline)) {  // the columns fetched last into list u
+  auto list_rows = [&](int u) __attribute__((always_inline)) {  // the columns fetched last, list u, from their query rows
     int t, h;
     column(l_c, l_t, l_h, t, h);
-    const uint32_t row = (uint32_t)f_row * (uint32_t)p.Hq + (uint32_t)(kvh * G + h);
+    const uint32_t row = cols[u].row[lane] * (uint32_t)p.Hq + (uint32_t)(kvh * G + h);
     cols[u].row[lane] = WIDE ? row : row * (2 * D);
     cols[u].val[lane] = WIDE ? row : row * 4;
     cols[u].lim[lane] = WIDE ? (uint32_t)(b.lim_begin + t) : 4 * (uint32_t)(b.lim_begin + t);
@@ -629,18 +634,29 @@ __global__ __launch_bounds__(kThreads) void bwd_dkdv_kernel(BwdParams p) {
 
   // Step t computes stage t % 3, loaded at step t-2, and loads the columns of
   // step t+2 into the stage of step t-1, which every wavefront has read
-  // before this step's barrier; their list was written at step t-1, and the
-  // list of step t+3 is written now, where step t-1's was.  Before the barrier
-  // each wavefront waits for its own loads of step t (at most the 2*IPW+1 of
-  // step t+1 may still be in flight) and wavefront 7 for its list's stores.
+  // before this step's barrier; their list was written at step t-1.  Wavefront
+  // 7 writes the list of step t+3 now, from the query rows it fetched at step
+  // t-1, and fetches those of step t+4 to where list t was, which was read at
+  // step t-2.  Before the barrier each wavefront waits for its own loads of
+  // step t and wavefront 7 for its list's stores; at most the 2*IPW+1 loads of
+  // step t+1 are still in flight (the rows were fetched before them).
   const int n_steps = (c_end - c_begin + COLS - 1) / COLS;
   if (wave == 7) {
 #pragma unroll
     for (int u = 0; u < 3; ++u) {
-      fetch_rows();
+      fetch_rows(u);
+      tile::wait_vm<0>();
+      asm volatile("" ::: "memory");
       list_rows(u);
     }
-    fetch_rows();
+    fetch_rows(3);
+  }
+  // K and V are waited for here: pending into the loop, their waits there
+  // would be for every load in flight.
+#pragma unroll
+  for (int kk = 0; kk < NKK; ++kk) {
+    asm volatile("" : "+v"(bv[kk]));
+    if (kk < NKR) asm volatile("" : "+v"(bk[kk]));
   }
   __syncthreads();
   load(0, 0);
@@ -651,11 +667,11 @@ __global__ __launch_bounds__(kThreads) void bwd_dkdv_kernel(BwdParams p) {
     if (wave == 7) __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
     tile::bar();
     auto feed = [&]() __attribute__((always_inline)) {
-      load((t + 2) & 3, s == 0 ? 2 : s - 1);
       if (wave == 7) {
         list_rows((t + 3) & 3);
-        fetch_rows();
+        fetch_rows(t & 3);
       }
+      load((t + 2) & 3, s == 0 ? 2 : s - 1);
     };
     if (idle)
       feed();
