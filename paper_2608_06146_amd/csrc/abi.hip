@@ -2,6 +2,7 @@
 // caller's workspace, and the kernel launches on the caller's stream.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstring>
 #include <mutex>
 
@@ -411,6 +412,8 @@ extern "C" padoc_status padoc_tree_attn_bwd(const padoc_plan* plan, const void* 
   bp.G = plan->G;
   bp.scale = plan->scale;
   bp.scale_log2 = plan->scale * 1.4426950408889634f;
+  bp.scale_kv = std::max(plan->scale, 1e-36f);
+  bp.scale_kv_log2 = bp.scale_kv * 1.4426950408889634f;
   if (t_ev_before && t_ev_after) {
     e = hipEventRecord(t_ev_before, stream);
     if (e != hipSuccess) return hip_fail("hipEventRecord", e);

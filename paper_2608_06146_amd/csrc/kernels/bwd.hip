@@ -131,7 +131,7 @@ __global__ __launch_bounds__(kThreads) void bwd_dq_kernel(BwdParams p) {
     lse2 = lse * kLog2e;
     if (valid && hf == 0) {
       p.nd[row] = -dcol;
-      p.nl[row] = -lse / p.scale;
+      p.nl[row] = -lse / p.scale_kv;
     }
   }
   const float sl2 = p.scale_log2;
@@ -513,7 +513,7 @@ __global__ __launch_bounds__(kThreads) void bwd_dkdv_kernel(BwdParams p) {
       dk[db][i] = 0.f;
       dv[db][i] = 0.f;
     }
-  const float sl2 = p.scale_log2;
+  const float sl2 = p.scale_kv_log2;
 
   // Fragment reads as LDS byte addresses: a per-lane base, and the d block by
   // exclusive-or (a row is a multiple of 16 * CPR bytes and the swizzle is one),

@@ -72,7 +72,7 @@ struct BwdParams {
   void* dk;          // [T, Hkv, D]
   void* dv;
   float* nd;         // workspace [n_q, Hq]: -sum_d dout * o
-  float* nl;         // workspace [n_q, Hq]: -lse / scale
+  float* nl;         // workspace [n_q, Hq]: -lse / scale_kv
   float* part;       // workspace [slots][2: dK, dV][kBwdKeys][D] fp32: sums of the pieces of split key runs
   const WorkRec* work;  // the forward's query-major items (dQ)
   const RangeRec* ranges;
@@ -87,6 +87,10 @@ struct BwdParams {
   int32_t n_btokens, n_breduce;
   int32_t Hq, Hkv, G;
   float scale, scale_log2;
+  // dK/dV: its scores start at -lse / scale, so its scale is at least 1e-36,
+  // where that stays finite (at smaller ones, scale * q.k up to q.k = 1e28 is
+  // below fp32's last bit beside lse).
+  float scale_kv, scale_kv_log2;
 };
 
 struct CombineParams {

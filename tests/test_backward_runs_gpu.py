@@ -37,6 +37,27 @@ def test_split_runs_are_summed_in_order(d):
     assert all(torch.equal(x, y) for x, y in zip(first, again))
 
 
+@pytest.mark.parametrize("scale", [1e-35, 1e-37, 2e-38, 1.2e-38])
+def test_scales_at_which_lse_over_scale_leaves_fp32(scale):
+    """LSE / scale, from which dK/dV's scores start, passes 3.4e38 at the
+    smallest scales a plan takes; the probabilities are those of a plain mean.
+    Tolerance: P and the result are bf16 (2^-9 each, relative) on sums of n
+    terms of rms 1/i."""
+    n, d = 150, 128
+    q, k, v, do = (syn.draw_normal((n, 2, d), 11, i, "bf16", device="cuda") for i in range(4))
+    segs = pa.segments_layout([(-1, 0, n, n)], 0)
+    plan = pa.TreePlan(segs, 2, 2, d, "bf16", 0, softmax_scale=scale, num_kv_rows=n, num_q_rows=n)
+    o, lse = pa.tree_attn_fwd(q, k, v, plan)
+    assert torch.allclose(lse.double().cpu(), torch.arange(1, n + 1).double().log()[:, None].expand(n, 2), atol=1e-5)
+    dq, dk, dv = pa.tree_attn_bwd(q, k, v, o, lse, do, plan)
+    torch.cuda.synchronize()
+    P = torch.ones(n, n, dtype=torch.float64).tril() / torch.arange(1, n + 1)[:, None]
+    want = torch.einsum("ij,ihd->jhd", P, do.double().cpu())
+    err = (dv.double().cpu() - want).norm() / want.norm()
+    assert err < 2 ** -8, float(err)
+    assert all(bool(torch.isfinite(g).all()) for g in (dq, dk))
+
+
 def test_rows_without_queries_are_zero():
     """Gaps between segments, and keys that no query sees, get zero gradients
     whatever the buffers held."""
