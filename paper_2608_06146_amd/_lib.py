@@ -104,7 +104,7 @@ def lib():
         raise RuntimeError(f"{LIB_PATH} is missing: build it with `python -m paper_2608_06146_amd.build` "
                            "(the HIP library is required; there is no fallback path)")
     L = C.CDLL(LIB_PATH)
-    from . import _streams  # noqa: F401  (built with it; not during the first session)
+    _native_streams()  # now, not during the first session
     vp, i32, i64, sz = C.c_void_p, C.c_int32, C.c_int64, C.c_size_t
     L.padoc_tree_from_pages.argtypes = [C.POINTER(Page), i32, i32, vp, i32, C.POINTER(i32)]
     L.padoc_tree_layout.argtypes = [vp, i32, i32]
@@ -156,12 +156,38 @@ class PadocError(RuntimeError):
         self.status = status
 
 
+def _native_streams():
+    """The class of the module ``_streams``, or None where it is not built for
+    this interpreter (the library itself is plain C, for any)."""
+    try:
+        from ._streams import Streams
+    except ImportError:
+        return None
+    return Streams
+
+
+class CtypesStreams:
+    """What ``_streams`` does, through ctypes (about 1 us more a call)."""
+
+    def __init__(self, handle):
+        self.handle = handle
+
+    def open(self, parent, fork) -> int:
+        i = C.c_int32(0)
+        return lib().padoc_session_open(self.handle, int(parent), int(fork), C.byref(i)) or i.value
+
+    def close(self, stream_id) -> int:
+        return lib().padoc_session_close(self.handle, int(stream_id))
+
+
 def streams(handle):
-    """The native ``open`` / ``close`` of session ``handle``'s streams."""
-    L = lib()
-    from ._streams import Streams  # loaded with the library
-    return Streams(handle.value, C.cast(L.padoc_session_open, C.c_void_p).value,
-                   C.cast(L.padoc_session_close, C.c_void_p).value)
+    """``open`` (the id, or a negative status) and ``close`` (the status) of
+    session ``handle``'s streams."""
+    L, native = lib(), _native_streams()
+    if native is None:
+        return CtypesStreams(handle)
+    return native(handle.value, C.cast(L.padoc_session_open, C.c_void_p).value,
+                  C.cast(L.padoc_session_close, C.c_void_p).value)
 
 
 def check(status: int) -> None:

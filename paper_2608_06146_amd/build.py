@@ -1,5 +1,6 @@
 """Build ``libpadoc_attn.so`` in-tree with hipcc for gfx950, and the small
-CPython module ``_streams`` beside it.
+CPython module ``_streams`` beside it (where Python's headers are; the package
+calls the library through ctypes without it).
 
     python -m paper_2608_06146_amd.build            # incremental
     python -m paper_2608_06146_amd.build --force    # rebuild everything
@@ -25,6 +26,7 @@ LIB = os.path.join(PKG, "libpadoc_attn.so")
 STREAMS = os.path.join(PKG, "_streams" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 ARCH = os.environ.get("PADOC_OFFLOAD_ARCH", "gfx950")
 
+STREAMS_SOURCE = "csrc/python/streams.cpp"
 SOURCES = [
     "csrc/host/plan.cpp",
     "csrc/host/session.cpp",
@@ -82,8 +84,22 @@ def _compile(cc: str, src: str, force: bool) -> str:
     return obj
 
 
+def _compile_streams(cc: str, out: str) -> bool:
+    """``_streams`` into file `out`; False where there are no Python headers."""
+    inc = sysconfig.get_paths()["include"]
+    if not os.path.exists(os.path.join(inc, "Python.h")):
+        return False
+    cmd = [cc, "-O2", "-std=c++17", "-fPIC", "-Wall", "-shared", "-no-hip-rt", "-I", inc, "-o", out,
+           os.path.join(PKG, STREAMS_SOURCE)]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"compile failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
+    return True
+
+
 def build(force: bool = True, verbose: bool = False) -> str:
-    """Compile every source and link the shared library; returns its path."""
+    """Compile every source and link the shared library; returns its path.
+    What was built before is replaced only once everything has compiled."""
     cc = hipcc()
     os.makedirs(BUILD, exist_ok=True)
     with cf.ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
@@ -93,14 +109,12 @@ def build(force: bool = True, verbose: bool = False) -> str:
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
+    have_streams = _compile_streams(cc, STREAMS + ".tmp")
     os.replace(tmp, LIB)
-    tmp = STREAMS + ".tmp"
-    cmd = [cc, "-O2", "-std=c++17", "-fPIC", "-Wall", "-shared", "-no-hip-rt", "-I", sysconfig.get_paths()["include"], "-o", tmp,
-           os.path.join(PKG, "csrc/python/streams.cpp")]
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    if r.returncode != 0:
-        raise RuntimeError(f"link failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
-    os.replace(tmp, STREAMS)
+    if have_streams:
+        os.replace(STREAMS + ".tmp", STREAMS)
+    elif os.path.exists(STREAMS):
+        os.remove(STREAMS)  # of other sources
     if verbose:
         print(f"built {LIB}")
     return LIB

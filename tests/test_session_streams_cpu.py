@@ -1,12 +1,14 @@
 """Stream opening and closing through the native module against the C calls
 through ctypes, argument form by argument form."""
 import ctypes as C
+import os
+import sys
 
 import numpy as np
 import pytest
 
 import paper_2608_06146_amd as pa
-from paper_2608_06146_amd import _lib
+from paper_2608_06146_amd import _lib, build
 
 FORMS = [(-1, 0), (0, 0), (np.int64(0), np.int32(3)), (0.9, "4"), (True, False), (2**32 - 1, 0), (2**32, 2**33 + 5),
          (-(2**70) - 1, 0), (0, 6), (0, -1), (7, 0), (-2, 0), (None, 0), (0, None), ("x", 0), (float("nan"), 0)]
@@ -63,3 +65,49 @@ def test_destroyed_and_prepared():
     for f in (s.open, lambda: s.close(0)):
         with pytest.raises(ValueError, match="session is closed"):
             f()
+
+
+# ---------------------------------------------------------------- without the module
+
+@pytest.fixture
+def no_module(monkeypatch):
+    """An interpreter that the native module was not built for."""
+    monkeypatch.setitem(sys.modules, "paper_2608_06146_amd._streams", None)
+    monkeypatch.setattr(_lib, "_lib", None)
+
+
+def test_the_library_loads_without_the_module(no_module):
+    plan = pa.TreePlan(pa.segments_layout([(-1, 0, 10, 10)], 0), 2, 1, 64, "bf16", 0, num_kv_rows=10, num_q_rows=10)
+    assert plan.export()["work"].size and isinstance(twin()._streams, _lib.CtypesStreams)
+
+
+@pytest.mark.parametrize("parent,fork", FORMS)
+def test_open_close_without_the_module(no_module, parent, fork):
+    test_open_close_as_ctypes(parent, fork)
+    test_destroyed_and_prepared()
+
+
+@pytest.fixture
+def built(monkeypatch, tmp_path):
+    """build() of the present objects into another folder."""
+    if not os.path.exists(build.LIB):
+        pytest.skip("nothing is built")
+    for name in ("LIB", "STREAMS"):
+        monkeypatch.setattr(build, name, str(tmp_path / os.path.basename(getattr(build, name))))
+    return tmp_path
+
+
+def test_build_without_python_headers(built, monkeypatch):
+    monkeypatch.setattr(build.sysconfig, "get_paths", lambda: {"include": str(built)})
+    (built / os.path.basename(build.STREAMS)).write_text("old")
+    build.build(force=False)
+    assert os.path.exists(build.LIB) and not os.path.exists(build.STREAMS)
+
+
+def test_failed_build_replaces_nothing(built, monkeypatch):
+    bad = built / "bad.cpp"
+    bad.write_text("#error no\n")
+    monkeypatch.setattr(build, "STREAMS_SOURCE", str(bad))
+    with pytest.raises(RuntimeError, match="compile failed"):
+        build.build(force=False)
+    assert not os.path.exists(build.LIB) and not os.path.exists(build.STREAMS)
