@@ -977,9 +977,9 @@ void serialise_backward(padoc_plan& P) {
   P.bws_off_nl = align256(P.bws_off_blims + (size_t)P.n_btok * 4);
   P.bws_off_nd = align256(P.bws_off_nl + rows);
   P.bws_off_part = align256(P.bws_off_nd + rows);
-  const size_t part = (size_t)P.n_bwd_slots * 2 * kBwdKeys * P.D * 4;
-  const size_t floor = 2 * (size_t)P.num_kv_rows * P.Hkv * P.D * 4;  // what callers that size it themselves expect
-  P.bws_bytes = std::max<size_t>(256, align256(P.bws_off_part + std::max(part, floor)));
+  // one slot at least, so that the section's address lies in the workspace
+  const size_t part = (size_t)std::max<int64_t>(1, P.n_bwd_slots) * 2 * kBwdKeys * P.D * 4;
+  P.bws_bytes = align256(P.bws_off_part + part);
 }
 
 void serialise(padoc_plan& P) {
