@@ -31,16 +31,12 @@ __device__ __forceinline__ uint4 load_stream16(const void* p) {
   return make_uint4(t.x, t.y, t.z, t.w);
 }
 
-// Plain 16-byte load and store as one vector value (a uint4 struct copy
-// would become a memory-to-memory copy through a stack slot).
+// Plain 16-byte load as one vector value (a uint4 struct copy would become a
+// memory-to-memory copy through a stack slot).
 __device__ __forceinline__ uint4 load16(const void* p) {
   typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
   const u32x4 t = *static_cast<const u32x4*>(p);
   return make_uint4(t.x, t.y, t.z, t.w);
-}
-__device__ __forceinline__ void store16(void* p, const uint4& v) {
-  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-  *static_cast<u32x4*>(p) = u32x4{v.x, v.y, v.z, v.w};
 }
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -104,8 +100,6 @@ __device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) {
   u += 0x7fffu + ((u >> 16) & 1u);
   return (uint16_t)(u >> 16);
 }
-
-__device__ __forceinline__ float bf16_bits_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
 // Zero the bf16 elements at positions >= keep of an 8-element (16-byte)
 // chunk; keep may be <= 0 (all zero) or >= 8 (unchanged).

@@ -27,9 +27,11 @@
 // workgroup barrier) issues
 //   group A: S(t+1) = K(t+1) Q^T (16 MFMAs) with the exponentials, bf16
 //            conversions and row sums of tile t placed between them;
-//   group B: O^T += V(t)^T P(t)^T (16 MFMAs) with the scaling of S(t+1) to
-//            log2 units relative to the reference maximum and the loads of
-//            K(t+3), V(t+2) and the limit entries of tile t+3 between them.
+//   group B: O^T += V(t)^T P(t)^T (16 MFMAs) with the loads of K, V and the
+//            limit entries of tile t+3 between them.  The scaling of S(t+1) to
+//            log2 units relative to the reference maximum is written there
+//            too; the compiler moves it down, ahead of the next group A
+//            (held in place at d = 128 it measured the same).
 // Both wavefronts of a SIMD (waves w and w+4) run this, so the matrix core
 // alternates between them while each issues its vector work in the gaps (one
 // wavefront issues vector instructions at about half the rate two reach).
@@ -51,10 +53,11 @@
 //
 // Loads and waits.  Step t reads K(t+1), V(t) and the limits of tile t+1,
 // loaded at step t-2, and (on the slow path) K(t) and the limits of tile t;
-// its loads (K(t+3), V(t+2), limits of tile t+3) go to the stages of tiles
-// t-1 and t-2, so no stage a wavefront may still read is written.  Each wavefront waits for
-// its own loads of step t-2 (an immediate count: only the 2*IPW+1 loads of
-// step t-1 may still be in flight) before the barrier that starts step t.
+// its loads (K, V and limits of tile t+3) go to the stages of tile t-1, which
+// every wavefront has read before this step's barrier, so no stage that one may
+// still read is written.  Each wavefront waits for its own loads of step t-2
+// (an immediate count: only the 2*IPW+1 loads of step t-1 may still be in
+// flight) before the barrier that starts step t.
 // Every step issues the same loads (past the item's end they re-read a valid
 // tile into a stage nobody reads), so the counts are exact, and the item
 // waits for all of them before it ends.  Keys past a range's end read the

@@ -24,14 +24,6 @@ __device__ __forceinline__ int64_t uniform64(int64_t x) {
                    (uint32_t)__builtin_amdgcn_readfirstlane((int)x));
 }
 
-__device__ __forceinline__ RangeRec uniform_range(RangeRec r) {
-  r.kv_start = uniform64(r.kv_start);
-  r.n_keys = __builtin_amdgcn_readfirstlane(r.n_keys);
-  r.min_lim = __builtin_amdgcn_readfirstlane(r.min_lim);
-  r.lim_off = __builtin_amdgcn_readfirstlane(r.lim_off);
-  return r;
-}
-
 // Two transposing LDS reads (4 bf16 each) joined into one 8-element MFMA
 // operand: elements 0-3 from the read at lo, 4-7 from the read at hi.
 typedef short i16x4_t __attribute__((ext_vector_type(4)));

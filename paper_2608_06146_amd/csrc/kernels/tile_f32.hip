@@ -16,14 +16,16 @@
 // below are about 6 us at the rate of a large fp32 product.  Hence the key
 // split: a 448-key item of the small forward is 4 blocks a wavefront, not 7
 // tiles one after the other.  W = 8 packed (few, long items).  W = 4 paged: 4
-// wavefronts of 183 registers leave a compute unit room for two workgroups,
+// wavefronts of 252 registers (64 of them accumulation registers; 256 is the
+// most for this) leave a compute unit room for two workgroups,
 // of which one waits for its first keys while the other computes (decode step
 // of 4 pages of 1,152 shared keys and 16 branches, Hq 16, Hkv 2, d = 128,
 // schedule resident: 37 us with 8, 31 with 4).  Without the K block in flight
-// (141 registers) it was 32.
+// it was 32.
 // Measured against one thread per column on the vector units (paged) and
 // LDS-staged tiles with 8 interleaved key slices (packed), one MI355X, whole
-// calls: that decode step 2,080 -> 48 us; packed forward of 256 + 64 + 4 x 32
+// calls: that decode step 2,080 -> 48 us (33 since a kernel copies its
+// schedule); packed forward of 256 + 64 + 4 x 32
 // tokens, Hq 4, Hkv 1, d = 64: 31.8 -> 12.2 us (kernel 29 -> 9.4).
 //
 // Operand layout, lane (r, g) = (lane % 16, lane / 16), with every load one
