@@ -19,9 +19,11 @@
 #include <cstdio>
 #include <cstring>
 #include <functional>
+#include <iterator>
 #include <limits>
 #include <map>
 #include <memory>
+#include <numeric>
 #include <new>
 #include <tuple>
 #include <utility>
@@ -495,6 +497,8 @@ struct BwdRun {
 // candidates between a fifth of a unit's share of all blocks and no cut are
 // tried on the greedy assignment the dispatch makes of them, and the one with
 // the earliest end is taken (the longest on a tie); never under 64 blocks.
+// Candidates that cut no run are all alike, and the first: where there are no
+// others nothing is tried (2,000 small pages, 32 KV heads: a third of the plan).
 int64_t bwd_piece_blocks(const std::vector<BwdRun>& runs, int64_t G, int64_t Hkv, int64_t units) {
   int64_t total = 0, longest = 0;
   for (const BwdRun& r : runs) {
@@ -504,10 +508,15 @@ int64_t bwd_piece_blocks(const std::vector<BwdRun>& runs, int64_t G, int64_t Hkv
   }
   const int64_t share = ceil_div(total, units);
   if (runs.size() > 20000) return std::max<int64_t>(64, share);  // many more runs than units: already even
+  const double shares[] = {1.5, 1.2, 0.85, 0.6, 0.42, 0.3, 0.2};
+  auto cap_of = [&](double f) { return std::max<int64_t>(64, (int64_t)(f * (double)share)); };
+  const int64_t whole = std::max<int64_t>(64, longest);
+  if (cap_of(0.2) >= longest) return whole;
   int64_t best = 0, best_end = std::numeric_limits<int64_t>::max();
   std::vector<int64_t> cost, load;
-  for (const double f : {1e9, 1.5, 1.2, 0.85, 0.6, 0.42, 0.3, 0.2}) {
-    const int64_t cap = std::max<int64_t>(64, f > 1e6 ? longest : (int64_t)(f * (double)share));
+  for (int i = -1; i < (int)std::size(shares); ++i) {
+    const int64_t cap = i < 0 ? whole : cap_of(shares[i]);
+    if (i >= 0 && cap >= longest) continue;
     cost.clear();
     int64_t split = 0;
     for (const BwdRun& r : runs) {
@@ -573,7 +582,8 @@ bool build_backward(padoc_plan& P, const AncList& anc, int32_t target_workgroups
   P.n_btok = n_btok;
   const int64_t tw = target_workgroups > 0 ? target_workgroups : 1024;
   const int64_t cap = bwd_piece_blocks(runs, P.G, P.Hkv, std::max<int64_t>(1, std::min<int64_t>(tw / 4, 1 << 16)));
-  std::vector<std::pair<padoc::BwdRec, int32_t>> items;  // with their slots
+  P.bwd.reserve(runs.size() * (size_t)P.Hkv);
+  P.bwd_slot.reserve(runs.size() * (size_t)P.Hkv);
   for (const BwdRun& r : runs) {
     const int64_t cols = (int64_t)r.ntok * P.G;
     const int64_t blocks = ceil_div(cols, 32);
@@ -593,18 +603,39 @@ bool build_backward(padoc_plan& P, const AncList& anc, int32_t target_workgroups
         b.ncol = (int32_t)std::min<int64_t>(step, cols - c0);
         b.kvh = g;
         b.cost = (int32_t)ceil_div(b.ncol, 32);
-        items.push_back({b, n_slots > 0 ? (int32_t)(P.n_bwd_slots + (int64_t)g * n_slots + c0 / step) : -1});
+        P.bwd.push_back(b);
+        P.bwd_slot.push_back(n_slots > 0 ? (int32_t)(P.n_bwd_slots + (int64_t)g * n_slots + c0 / step) : -1);
       }
     }
     P.n_bwd_slots += (int64_t)n_slots * P.Hkv;
-    if (P.n_bwd_slots > kI32Max || (int64_t)items.size() > kI32Max) return false;
+    if (P.n_bwd_slots > kI32Max || (int64_t)P.bwd.size() > kI32Max) return false;
   }
-  std::stable_sort(items.begin(), items.end(), [](const auto& a, const auto& b) { return a.first.cost > b.first.cost; });
-  P.bwd.reserve(items.size());
-  P.bwd_slot.reserve(items.size());
-  for (const auto& it : items) {
-    P.bwd.push_back(it.first);
-    P.bwd_slot.push_back(it.second);
+  // costliest first
+  const auto costlier = [](const padoc::BwdRec& a, const padoc::BwdRec& b) { return a.cost > b.cost; };
+  if (!std::is_sorted(P.bwd.begin(), P.bwd.end(), costlier)) {
+    const size_t n_items = P.bwd.size();
+    std::vector<int32_t> at(n_items);  // where each item goes
+    int32_t mx = 0;
+    for (const auto& b : P.bwd) mx = std::max(mx, b.cost);
+    if (mx < 1 << 20) {  // counting sort
+      std::vector<int32_t> start((size_t)mx + 2, 0);
+      for (const auto& b : P.bwd) ++start[mx - b.cost + 1];
+      for (int32_t c = 0; c <= mx; ++c) start[c + 1] += start[c];
+      for (size_t i = 0; i < n_items; ++i) at[i] = start[mx - P.bwd[i].cost]++;
+    } else {
+      std::vector<int32_t> order(n_items);
+      std::iota(order.begin(), order.end(), 0);
+      std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return costlier(P.bwd[a], P.bwd[b]); });
+      for (size_t i = 0; i < n_items; ++i) at[order[i]] = (int32_t)i;
+    }
+    std::vector<padoc::BwdRec> bwd(n_items);
+    std::vector<int32_t> slot(n_items);
+    for (size_t i = 0; i < n_items; ++i) {
+      bwd[at[i]] = P.bwd[i];
+      slot[at[i]] = P.bwd_slot[i];
+    }
+    P.bwd.swap(bwd);
+    P.bwd_slot.swap(slot);
   }
   // Rows outside every run, in pieces of at most kBwdKeys.
   std::sort(runs.begin(), runs.end(), [](const BwdRun& a, const BwdRun& b) { return a.key_row0 < b.key_row0; });
